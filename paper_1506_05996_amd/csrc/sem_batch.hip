@@ -380,7 +380,7 @@ void batched_iteration(sem_batch b, int pc, hipStream_t s) {
 template <typename T>
 hipGraphExec_t capture_iteration(sem_batch b, int pc) {
   if (!b->cap) SEM_HIP(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
-  for (auto& g : b->groups) g.mesh->direct_coarse = true;
+  for (auto& g : b->groups) g.mesh->in_capture = true;
   hipGraph_t graph = nullptr;
   SEM_HIP(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
   try {
@@ -388,11 +388,11 @@ hipGraphExec_t capture_iteration(sem_batch b, int pc) {
   } catch (...) {
     (void)hipStreamEndCapture(b->cap, &graph);
     if (graph) (void)hipGraphDestroy(graph);
-    for (auto& g : b->groups) g.mesh->direct_coarse = false;
+    for (auto& g : b->groups) g.mesh->in_capture = false;
     throw;
   }
   SEM_HIP(hipStreamEndCapture(b->cap, &graph));
-  for (auto& g : b->groups) g.mesh->direct_coarse = false;
+  for (auto& g : b->groups) g.mesh->in_capture = false;
   hipGraphExec_t exec = nullptr;
   hipError_t err = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);

@@ -70,7 +70,7 @@ struct sem_mesh_s {
   bool fp32 = true;
   int device = 0;
   // numbering / gather
-  DBuf<int32_t> rec, vinc_off, vinc_ec, einc_off, cidx, order;
+  DBuf<int32_t> rec, vinc_off, einc_off, cidx, order;
   DBuf<uint8_t> dir, fcount;
   // operator
   DBuf<double> G64, D64, w64, X864, tq64;  // X8: vertex coordinates, tq: GLL points and weights
@@ -80,15 +80,13 @@ struct sem_mesh_s {
   DBuf<int32_t> ip, xdest;
   DBuf<double> S64, lam64, h64, zo64;
   DBuf<float> S32, lam32, h32, zo32;
-  // coarse: vectors in coarse order (R, y, Z, X), vertex-order solution Zv,
-  // the nested-dissection fronts and their work lists
-  DBuf<double> phi, Re, Rlev, Ylev, Wlev, Xlev, Zv;
+  // coarse: solution in coarse order X, in vertex order Zv, the contribution
+  // vector and the nested-dissection fronts with their tiles and index lists
+  DBuf<double> phi, Xlev, Zv;
   DBuf<double> fwd_pool, bwd_pool, cvec;
-  DBuf<FrontNode> fnodes;
-  DBuf<int32_t> fb_idx, ct_off, ct_pos, fy_items;
-  DBuf<RowItem> fr_items, br_items, fs_items;
-  hipGraphExec_t coarse_graph = nullptr;  // the solve sweeps, captured once per factorisation
-  bool direct_coarse = false;             // launch the sweeps directly (inside an enclosing capture)
+  DBuf<CoarseTile> tiles;
+  DBuf<int32_t> fb_idx, cvert, pslot, rs_off, part_dst, cdst, pre_slot, pre_row;
+  bool in_capture = false;                // inside an enclosing capture: no graph of its own
   int epb[2] = {0, 0};                    // operator tile (elements per workgroup) for FP64, FP32
   hipStream_t side_stream = nullptr;      // coarse chain of the preconditioner, beside the patch solves
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;

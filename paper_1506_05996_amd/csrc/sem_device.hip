@@ -366,7 +366,7 @@ int64_t schwarz_sum(sem_mesh m, T* z, bool fine, const double* Zv, hipStream_t s
 template <int N, typename T>
 void launch_restrict(sem_mesh m, const T* r, hipStream_t s) {
   hipLaunchKernelGGL((restrict_kernel<N, T>), dim3((unsigned)xcd_grid(m->T.E)), dim3((N + 1) * (N + 1)), 0, s, r,
-                     m->Re.p, m->rec.p, m->phi.p, m->order.p, m->T.E);
+                     m->cvec.p, m->part_dst.p, m->rec.p, m->phi.p, m->order.p, m->T.E);
   SEM_HIP(hipGetLastError());
 }
 
@@ -386,71 +386,47 @@ void fdm_and_restrict(sem_mesh m, const T* r, bool fine, bool coarse, hipStream_
   }
 }
 
-// one tiled launch of the forward (large nodes) or backward sweep at a height
-template <int RW, bool SPLIT>
-void launch_coarse_fwd_t(sem_mesh m, hipStream_t s, const RowItem* tiles, int64_t n) {
-  hipLaunchKernelGGL((coarse_fwd_kernel<RW, SPLIT>), dim3((unsigned)n), dim3(256), 0, s, m->Wlev.p, m->cvec.p,
-                     (const double*)m->Ylev.p, (const double*)m->fwd_pool.p, m->fnodes.p, tiles);
-}
-
-template <int RW, bool SPLIT>
-void launch_coarse_bwd_t(sem_mesh m, hipStream_t s, const RowItem* tiles, int64_t n) {
-  hipLaunchKernelGGL((coarse_bwd_kernel<RW, SPLIT>), dim3((unsigned)n), dim3(256), 0, s, m->Xlev.p,
-                     (const double*)m->Wlev.p, (const double*)m->bwd_pool.p, m->fb_idx.p, m->fnodes.p, tiles);
-}
-
-void launch_coarse_fwd(sem_mesh m, hipStream_t s, const CoarseTileShape& t, const RowItem* tiles, int64_t n) {
-  if (t.rw == 4)
-    launch_coarse_fwd_t<4, false>(m, s, tiles, n);
-  else if (!t.split)
-    launch_coarse_fwd_t<2, false>(m, s, tiles, n);
-  else
-    launch_coarse_fwd_t<2, true>(m, s, tiles, n);
-}
-
-void launch_coarse_bwd(sem_mesh m, hipStream_t s, const CoarseTileShape& t, const RowItem* tiles, int64_t n) {
-  if (t.rw == 4)
-    launch_coarse_bwd_t<4, false>(m, s, tiles, n);
-  else if (!t.split)
-    launch_coarse_bwd_t<2, false>(m, s, tiles, n);
-  else
-    launch_coarse_bwd_t<2, true>(m, s, tiles, n);
-}
-
-// Rlev (coarse order) -> Zv (vertex order): nested-dissection sweeps
-void coarse_sweeps(sem_mesh m, hipStream_t s) {
-  const HostTables& T = m->T;
-  const int H = T.n_heights;
-  for (int h = 0; h < H; ++h) {
-    const int64_t ny = T.fy_off[h + 1] - T.fy_off[h], nr = T.fr_off[h + 1] - T.fr_off[h];
-    const int64_t ns = T.fs_off[h + 1] - T.fs_off[h];
-    if (ny > 0)  // rows of the large nodes (small nodes assemble their own)
-      hipLaunchKernelGGL(coarse_assemble_kernel, dim3((unsigned)blocks_for(8 * ny)), dim3(kGS), 0, s, m->Ylev.p,
-                         (const double*)m->Rlev.p, (const double*)m->cvec.p, m->ct_off.p, m->ct_pos.p,
-                         m->fy_items.p + T.fy_off[h], ny);
-    if (ns > 0)
-      hipLaunchKernelGGL(coarse_fwd_small_kernel, dim3((unsigned)((ns + 3) / 4)), dim3(256), 0, s, m->Wlev.p,
-                         m->cvec.p, (const double*)m->Rlev.p, (const int32_t*)m->ct_off.p,
-                         (const int32_t*)m->ct_pos.p, (const double*)m->fwd_pool.p, m->fnodes.p,
-                         m->fs_items.p + T.fs_off[h], ns);
-    if (nr > 0)
-      launch_coarse_fwd(m, s, T.fr_shape[h], m->fr_items.p + T.fr_off[h], nr);
-    SEM_HIP(hipGetLastError());
+// one launch of the forward or backward sweep
+template <int RW, bool NARROW>
+void launch_coarse_tiles(sem_mesh m, hipStream_t s, const CoarseLaunch& L, bool forward) {
+  const CoarseTile* tiles = m->tiles.p + L.first;
+  if (forward) {
+    const int n_pre = L.first == 0 ? (int)m->T.pre_row.size() : 0;  // the lowest launch sums the higher rows' parts
+    hipLaunchKernelGGL((coarse_fwd_kernel<RW, NARROW>), dim3((unsigned)(L.count + (n_pre + 255) / 256)), dim3(256), 0,
+                       s, m->Xlev.p, m->Zv.p, m->cvec.p, (const double*)m->fwd_pool.p, tiles,
+                       (const int32_t*)m->rs_off.p, (const int32_t*)m->cdst.p, (const int32_t*)m->cvert.p,
+                       (int)L.count, (const int32_t*)m->pre_slot.p, (const int32_t*)m->pre_row.p, n_pre);
+  } else {
+    hipLaunchKernelGGL((coarse_bwd_kernel<RW, NARROW>), dim3((unsigned)L.count), dim3(256), 0, s, m->Xlev.p, m->Zv.p,
+                       (const double*)m->bwd_pool.p, tiles, (const int32_t*)m->fb_idx.p, (const int32_t*)m->cvert.p);
   }
-  for (int h = H - 1; h >= 0; --h) {
-    const int64_t nb = T.br_off[h + 1] - T.br_off[h];
-    if (nb == 0) continue;
-    launch_coarse_bwd(m, s, T.br_shape[h], m->br_items.p + T.br_off[h], nb);
-    SEM_HIP(hipGetLastError());
-  }
-  hipLaunchKernelGGL(coarse_scatter_kernel, dim3((unsigned)blocks_for(T.V)), dim3(kGS), 0, s, m->Zv.p, m->Xlev.p,
-                     m->cidx.p, T.V);
   SEM_HIP(hipGetLastError());
 }
 
+void launch_coarse(sem_mesh m, hipStream_t s, const CoarseLaunch& L, bool forward) {
+  if (!L.wide) {
+    switch (L.rw) {
+      case 1: return launch_coarse_tiles<1, true>(m, s, L, forward);
+      case 2: return launch_coarse_tiles<2, true>(m, s, L, forward);
+      case 4: return launch_coarse_tiles<4, true>(m, s, L, forward);
+      default: return launch_coarse_tiles<8, true>(m, s, L, forward);
+    }
+  }
+  switch (L.rw) {
+    case 1: return launch_coarse_tiles<1, false>(m, s, L, forward);
+    case 2: return launch_coarse_tiles<2, false>(m, s, L, forward);
+    default: return launch_coarse_tiles<4, false>(m, s, L, forward);
+  }
+}
+
+// element parts in the contribution vector -> Zv (vertex order; 0 on Dirichlet
+// vertices since set-up): nested-dissection sweeps
+void coarse_sweeps(sem_mesh m, hipStream_t s) {
+  for (const CoarseLaunch& L : m->T.fwd_launch) launch_coarse(m, s, L, true);
+  for (const CoarseLaunch& L : m->T.bwd_launch) launch_coarse(m, s, L, false);
+}
+
 void release_coarse_graph(sem_mesh m) {
-  if (m->coarse_graph) (void)hipGraphExecDestroy(m->coarse_graph);
-  m->coarse_graph = nullptr;
   if (m->amg_graph) (void)hipGraphExecDestroy(m->amg_graph);
   m->amg_graph = nullptr;
 }
@@ -538,63 +514,52 @@ void amg_fcg2(sem_mesh m, int l, const double* b, double* x, hipStream_t s) {
   SEM_HIP(hipGetLastError());
 }
 
-// Rlev (coarse order) -> Zv (vertex order) by one K-cycle
+// element parts in the contribution vector -> Zv (vertex order) by one K-cycle
 void amg_sweeps(sem_mesh m, hipStream_t s) {
   const HostTables& T = m->T;
   auto& d0 = *m->amg[0];
-  hipLaunchKernelGGL(amg_in_kernel, dim3((unsigned)blocks_for(d0.n)), dim3(kGS), 0, s, d0.B.p, m->Rlev.p,
-                     m->amg_nd.p, d0.n);
+  hipLaunchKernelGGL(amg_in_kernel, dim3((unsigned)blocks_for(d0.n)), dim3(kGS), 0, s, d0.B.p, m->cvec.p, m->rs_off.p,
+                     m->pslot.p, m->cvert.p, m->vinc_off.p, m->amg_nd.p, d0.n);
   amg_kcycle(m, 0, d0.B.p, d0.X.p, s);
   hipLaunchKernelGGL(amg_out_kernel, dim3((unsigned)blocks_for(T.V)), dim3(kGS), 0, s, m->Zv.p, d0.X.p, m->cidx.p,
                      m->amg_pos.p, T.V);
   SEM_HIP(hipGetLastError());
 }
 
-// Capture the coarse solve of the current coarse solver (nested-dissection
-// sweeps or one K-cycle) once, on a private stream; the preconditioner replays
-// it on the caller's stream.  Built at set-up and whenever the coarse matrix or
-// solver changes.
+// Capture one K-cycle (some 200 small launches) once, on a private stream; the
+// preconditioner replays it on the caller's stream.  Built at set-up and
+// whenever the coarse matrix or solver changes.  The exact solve needs none:
+// it is a handful of launches.
 void build_coarse_graph(sem_mesh m) {
-  if (m->T.nc == 0) return;
-  const bool amg = m->coarse_solver == SEM_COARSE_AMG;
-  if (amg && m->amg.empty()) throw Error{SEM_EINVAL, "AMG hierarchy not built"};
-  hipGraphExec_t& exec = amg ? m->amg_graph : m->coarse_graph;
-  if (exec) return;
+  if (m->T.nc == 0 || m->coarse_solver != SEM_COARSE_AMG) return;
+  if (m->amg.empty()) throw Error{SEM_EINVAL, "AMG hierarchy not built"};
+  if (m->amg_graph) return;
   if (m->no_alloc) throw Error{SEM_EINVAL, "coarse-solve graph missing (it is built at set-up)"};
   if (!m->capture_stream) SEM_HIP(hipStreamCreateWithFlags(&m->capture_stream, hipStreamNonBlocking));
   hipGraph_t g = nullptr;
   SEM_HIP(hipStreamBeginCapture(m->capture_stream, hipStreamCaptureModeThreadLocal));
   try {
-    if (amg)
-      amg_sweeps(m, m->capture_stream);
-    else
-      coarse_sweeps(m, m->capture_stream);
+    amg_sweeps(m, m->capture_stream);
   } catch (...) {
     (void)hipStreamEndCapture(m->capture_stream, &g);
     if (g) (void)hipGraphDestroy(g);
     throw;
   }
   SEM_HIP(hipStreamEndCapture(m->capture_stream, &g));
-  hipError_t err = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
+  hipError_t err = hipGraphInstantiate(&m->amg_graph, g, nullptr, nullptr, 0);
   (void)hipGraphDestroy(g);
   if (err != hipSuccess) {
-    exec = nullptr;
+    m->amg_graph = nullptr;
     throw Error{SEM_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(err)};
   }
 }
 
-// Rlev (coarse order) -> Zv (vertex order): the coarse solve P_0
+// element parts in the contribution vector -> Zv (vertex order): the coarse solve P_0
 void coarse_solve_tree(sem_mesh m, hipStream_t s) {
-  const bool amg = m->coarse_solver == SEM_COARSE_AMG;
-  if (m->direct_coarse) {  // inside an enclosing capture: launch the kernels themselves
-    if (amg)
-      amg_sweeps(m, s);
-    else
-      coarse_sweeps(m, s);
-    return;
-  }
+  if (m->coarse_solver != SEM_COARSE_AMG) return coarse_sweeps(m, s);
+  if (m->in_capture) return amg_sweeps(m, s);  // inside an enclosing capture: the kernels themselves
   build_coarse_graph(m);
-  SEM_HIP(hipGraphLaunch(amg ? m->amg_graph : m->coarse_graph, s));
+  SEM_HIP(hipGraphLaunch(m->amg_graph, s));
 }
 
 // the second stream (and its fork/join events) that runs the coarse chain
@@ -638,33 +603,27 @@ void precond_dot(sem_mesh m, const T* r, T* z, int pc, int dot_dst, int dot_mode
   // The coarse and fine parts are independent until the final sum: the
   // coarse chain (restriction, coarse sweeps) runs on a second stream while
   // the patch solves run on the caller's stream; both join before the sum.
-  // The patch solves are issued first, so that the host's launches of the
-  // coarse chain do not hold them back.
-  hipStream_t sc = s;
+  // The coarse chain is issued first: it is the longer dependent chain on all
+  // but the largest meshes, and its workgroups otherwise queue behind the patch
+  // solves', which fill every CU.
   if (coarse_started) {
     fdm_and_restrict<T>(m, r, true, false, s);
     SEM_HIP(hipStreamWaitEvent(s, m->ev_join, 0));
-  } else if (coarse && fine) {
-    ensure_side_stream(m);
-    SEM_HIP(hipEventRecord(m->ev_fork, s));
-    SEM_HIP(hipStreamWaitEvent(m->side_stream, m->ev_fork, 0));
-    sc = m->side_stream;
-  }
-  if (coarse_started) {
-    // fine part and join done above
   } else {
-  if (fine) fdm_and_restrict<T>(m, r, true, false, s);
-  if (coarse) {
-    fdm_and_restrict<T>(m, r, false, true, sc);
-    hipLaunchKernelGGL(restrict_gather_kernel, dim3((unsigned)blocks_for(H.V)), dim3(kGS), 0, sc, m->Rlev.p, m->Re.p,
-                       m->vinc_off.p, m->vinc_ec.p, m->cidx.p, H.V);
-    SEM_HIP(hipGetLastError());
-    coarse_solve_tree(m, sc);
-  }
-  if (sc != s) {
-    SEM_HIP(hipEventRecord(m->ev_join, sc));
-    SEM_HIP(hipStreamWaitEvent(s, m->ev_join, 0));
-  }
+    hipStream_t sc = s;
+    if (coarse && fine) {
+      ensure_side_stream(m);
+      SEM_HIP(hipEventRecord(m->ev_fork, s));
+      SEM_HIP(hipStreamWaitEvent(m->side_stream, m->ev_fork, 0));
+      sc = m->side_stream;
+    }
+    if (coarse) {
+      fdm_and_restrict<T>(m, r, false, true, sc);
+      coarse_solve_tree(m, sc);
+      if (sc != s) SEM_HIP(hipEventRecord(m->ev_join, sc));
+    }
+    if (fine) fdm_and_restrict<T>(m, r, true, false, s);
+    if (sc != s) SEM_HIP(hipStreamWaitEvent(s, m->ev_join, 0));
   }
   if (dot_dst < 0) {
     schwarz_sum<T>(m, z, fine, coarse ? (const double*)m->Zv.p : nullptr, s);
@@ -675,14 +634,14 @@ void precond_dot(sem_mesh m, const T* r, T* z, int pc, int dot_dst, int dot_mode
 }
 
 // PCG's update of r fused with the coarse restriction (update_r_restrict_kernel),
-// r . r into scalar slot 4, then the rest of the coarse chain (vertex sums,
-// coarse solve) forked onto the side stream; precond_dot(..., true) joins it.
+// r . r into scalar slot 4, then the rest of the coarse chain (the coarse
+// solve) forked onto the side stream; precond_dot(..., true) joins it.
 template <int N, typename T>
 int64_t launch_update_r_restrict(sem_mesh m, T* r, const T* w, hipStream_t s) {
   const int64_t grid = xcd_grid(m->T.E);
   hipLaunchKernelGGL((update_r_restrict_kernel<N, T>), dim3((unsigned)grid), dim3((N + 1) * (N + 1)), 0, s, r, w,
-                     (const double*)m->wk.sc, m->Re.p, m->wk.dpart, m->rec.p, (const double*)m->phi.p, m->order.p,
-                     m->T.E);
+                     (const double*)m->wk.sc, m->cvec.p, m->part_dst.p, m->wk.dpart, m->rec.p,
+                     (const double*)m->phi.p, m->order.p, m->T.E);
   SEM_HIP(hipGetLastError());
   return grid;
 }
@@ -702,14 +661,10 @@ void update_r_and_fork_coarse(sem_mesh m, T* r, const T* w, hipStream_t s) {
       throw Error{SEM_EUNSUPPORTED, "order not compiled"};
   }
   reduce_partials(m, n, 4, 0, s);
-  const HostTables& H = m->T;
   ensure_side_stream(m);
   hipStream_t sc = m->side_stream;
   SEM_HIP(hipEventRecord(m->ev_fork, s));
   SEM_HIP(hipStreamWaitEvent(sc, m->ev_fork, 0));
-  hipLaunchKernelGGL(restrict_gather_kernel, dim3((unsigned)blocks_for(H.V)), dim3(kGS), 0, sc, m->Rlev.p, m->Re.p,
-                     m->vinc_off.p, m->vinc_ec.p, m->cidx.p, H.V);
-  SEM_HIP(hipGetLastError());
   coarse_solve_tree(m, sc);
   SEM_HIP(hipEventRecord(m->ev_join, sc));
 }
@@ -724,48 +679,44 @@ void factor_coarse(sem_mesh m) {
   release_coarse_graph(m);
   if (m->coarse_solver == SEM_COARSE_AMG) amg_setup(m);
   m->cidx.upload(T.cidx.data(), T.cidx.size());
-  const size_t nc = std::max<int64_t>(T.nc, 1);
-  m->Rlev.alloc(nc);
-  m->Ylev.alloc(nc);
-  m->Wlev.alloc(nc);
-  m->Xlev.alloc(nc);
+  m->part_dst.upload(T.part_dst.data(), T.part_dst.size());
+  m->cvec.alloc(std::max<int64_t>(T.c_size, 1));
+  m->Xlev.alloc(std::max<int64_t>(T.nc, 1));
+  SEM_HIP(hipMemset(m->Zv.p, 0, m->Zv.n * sizeof(double)));  // Dirichlet vertices stay 0
   if (T.nc == 0) {
     m->fwd_pool.release();
     m->bwd_pool.release();
+    SEM_HIP(hipDeviceSynchronize());
     return;
   }
   // fronts are factored densely: bound their size
   if (T.max_front > 16384)
     throw Error{SEM_EUNSUPPORTED, "coarse front of " + std::to_string(T.max_front) + " vertices exceeds 16384"};
-  m->fnodes.upload(T.fnodes.data(), T.fnodes.size());
+  m->tiles.upload(T.tiles.data(), T.tiles.size());
   m->fb_idx.upload(T.fb_idx.data(), T.fb_idx.size());
-  m->ct_off.upload(T.ct_off.data(), T.ct_off.size());
-  m->ct_pos.upload(T.ct_pos.data(), T.ct_pos.size());
-  m->fy_items.upload(T.fy_items.data(), T.fy_items.size());
-  m->fr_items.upload(T.fr_items.data(), T.fr_items.size());
-  m->br_items.upload(T.br_items.data(), T.br_items.size());
-  m->fs_items.upload(T.fs_items.data(), T.fs_items.size());
-  m->cvec.alloc(std::max<int64_t>(T.c_size, 1));
+  m->cvert.upload(T.cvert.data(), T.cvert.size());
+  m->pslot.upload(T.pslot.data(), T.pslot.size());
+  m->pre_slot.upload(T.pre_slot.data(), T.pre_slot.size());
+  m->pre_row.upload(T.pre_row.data(), T.pre_row.size());
+  m->rs_off.upload(T.rs_off.data(), T.rs_off.size());
+  m->cdst.upload(T.cdst.data(), T.cdst.size());
   m->fwd_pool.alloc(T.fwd_size);
   m->bwd_pool.alloc(std::max<int64_t>(T.bwd_size, 1));
+  // the padding entry of odd rows is read (against a zero): keep it finite
+  SEM_HIP(hipMemset(m->fwd_pool.p, 0, m->fwd_pool.n * sizeof(double)));
+  SEM_HIP(hipMemset(m->bwd_pool.p, 0, m->bwd_pool.n * sizeof(double)));
   rocblas_handle hb;
   if (rocblas_create_handle(&hb) != rocblas_status_success) throw Error{SEM_EHIP, "rocblas_create_handle failed"};
   std::unique_ptr<std::remove_pointer<rocblas_handle>::type, decltype(&rocblas_destroy_handle)> guard(
       hb, rocblas_destroy_handle);
-  const int64_t mf = T.max_front;
-  DBuf<double> Fd, Ust;
-  DBuf<int32_t> mapd;
-  DBuf<rocblas_int> info;
-  info.alloc(1);
-  Fd.alloc((size_t)mf * mf);
-  Ust.alloc(std::max<int64_t>(T.ustack_size, 1));
-  mapd.alloc((size_t)mf);
-  std::vector<double> cols;
-  std::vector<int32_t> map;
-  std::vector<int64_t> u_at(T.fnodes.size(), -1);  // update matrix position in the stack
-  int64_t top = 0;
-  const double one = 1.0, zero = 0.0, mone = -1.0;
-  for (size_t q = 0; q < T.fnodes.size(); ++q) {
+  // positions of every front's entries of A_c (columns of its own vertices;
+  // entries towards eliminated vertices were taken by the descendants' fronts)
+  // and of every child's boundary in its parent's front, in one upload
+  const size_t nn = T.fnodes.size();
+  std::vector<int32_t> pos, map;
+  std::vector<double> val;
+  std::vector<int64_t> a_at(nn + 1, 0), map_at(nn, 0);
+  for (size_t q = 0; q < nn; ++q) {
     const FrontNode& F = T.fnodes[q];
     const int64_t s = F.s, b = F.b, f = s + b, end = F.off + s;
     const int32_t* B = T.fb_idx.data() + F.bidx;
@@ -775,17 +726,42 @@ void factor_coarse(sem_mesh m) {
       if (p == B + b || *p != g) throw Error{SEM_EMESH, "coarse front: entry outside the node's front"};
       return s + (p - B);
     };
-    // columns of the own vertices: A_c(idx, own) (entries towards eliminated
-    // vertices were taken by the descendants' fronts)
-    cols.assign((size_t)f * s, 0.0);
     for (int64_t r = 0; r < s; ++r)
       for (int32_t k = T.ac_off[F.off + r]; k < T.ac_off[F.off + r + 1]; ++k) {
         if (T.ac_col[k] < F.off) continue;
-        cols[(size_t)r * f + local(T.ac_col[k])] = T.ac_val[k];
+        pos.push_back((int32_t)(r * f + local(T.ac_col[k])));
+        val.push_back(T.ac_val[k]);
       }
-    SEM_HIP(hipMemcpy(Fd.p, cols.data(), cols.size() * sizeof(double), hipMemcpyHostToDevice));
+    a_at[q + 1] = (int64_t)pos.size();
+    for (int32_t c : T.fchildren[q]) {
+      const FrontNode& C = T.fnodes[c];
+      map_at[c] = (int64_t)map.size();
+      for (int32_t k = 0; k < C.b; ++k) map.push_back((int32_t)local(T.fb_idx[C.bidx + k]));
+    }
+  }
+  const int64_t mf = T.max_front;
+  DBuf<double> Fd, Ust, vald;
+  DBuf<int32_t> posd, mapd;
+  DBuf<rocblas_int> info;
+  posd.upload(pos.data(), pos.size());
+  vald.upload(val.data(), val.size());
+  mapd.upload(map.data(), map.size());
+  info.alloc(2 * nn);
+  SEM_HIP(hipMemset(info.p, 0, 2 * nn * sizeof(rocblas_int)));
+  Fd.alloc((size_t)mf * mf);
+  Ust.alloc(std::max<int64_t>(T.ustack_size, 1));
+  std::vector<int64_t> u_at(nn, -1);  // update matrix position in the stack
+  int64_t top = 0;
+  const double one = 1.0, zero = 0.0, mone = -1.0;
+  for (size_t q = 0; q < nn; ++q) {
+    const FrontNode& F = T.fnodes[q];
+    const int64_t s = F.s, b = F.b, f = s + b;
+    SEM_HIP(hipMemsetAsync(Fd.p, 0, (size_t)f * f * sizeof(double), 0));
+    const int64_t na = a_at[q + 1] - a_at[q];
+    hipLaunchKernelGGL(front_scatter_kernel, dim3((unsigned)blocks_for(na)), dim3(kGS), 0, 0, Fd.p,
+                       (const int32_t*)posd.p + a_at[q], (const double*)vald.p + a_at[q], na);
+    SEM_HIP(hipGetLastError());
     if (b > 0) {
-      SEM_HIP(hipMemset(Fd.p + s * f, 0, (size_t)b * f * sizeof(double)));
       hipLaunchKernelGGL(front_transpose_kernel, dim3((unsigned)blocks_for(s * b)), dim3(kGS), 0, 0, Fd.p, f, s, b);
       SEM_HIP(hipGetLastError());
     }
@@ -794,65 +770,52 @@ void factor_coarse(sem_mesh m) {
     for (int32_t c : T.fchildren[q]) {
       const FrontNode& C = T.fnodes[c];
       if (C.b == 0) continue;
-      map.resize(C.b);
-      for (int32_t k = 0; k < C.b; ++k) map[k] = (int32_t)local(T.fb_idx[C.bidx + k]);
-      SEM_HIP(hipMemcpy(mapd.p, map.data(), map.size() * sizeof(int32_t), hipMemcpyHostToDevice));
       hipLaunchKernelGGL(front_extend_add_kernel, dim3((unsigned)blocks_for((int64_t)C.b * C.b)), dim3(kGS), 0, 0,
-                         Fd.p, f, (const double*)Ust.p + u_at[c], (int64_t)C.b, (const int32_t*)mapd.p);
+                         Fd.p, f, (const double*)Ust.p + u_at[c], (int64_t)C.b, (const int32_t*)mapd.p + map_at[c]);
       SEM_HIP(hipGetLastError());
       if (first < 0 || u_at[c] < first) first = u_at[c];
     }
     if (first >= 0) top = first;
-    // S^-1 in place (lower triangle), mirrored
-    if (rocsolver_dpotrf(hb, rocblas_fill_lower, (rocblas_int)s, Fd.p, (rocblas_int)f, info.p) !=
+    // S^-1 in place (lower triangle), mirrored; the info values are checked at the end
+    if (rocsolver_dpotrf(hb, rocblas_fill_lower, (rocblas_int)s, Fd.p, (rocblas_int)f, info.p + 2 * q) !=
         rocblas_status_success)
       throw Error{SEM_EHIP, "rocsolver_dpotrf failed"};
-    rocblas_int ih = 0;
-    SEM_HIP(hipMemcpy(&ih, info.p, sizeof(ih), hipMemcpyDeviceToHost));
-    if (ih != 0) throw Error{SEM_EMESH, "coarse matrix is not positive definite"};
-    if (rocsolver_dpotri(hb, rocblas_fill_lower, (rocblas_int)s, Fd.p, (rocblas_int)f, info.p) !=
+    if (rocsolver_dpotri(hb, rocblas_fill_lower, (rocblas_int)s, Fd.p, (rocblas_int)f, info.p + 2 * q + 1) !=
         rocblas_status_success)
       throw Error{SEM_EHIP, "rocsolver_dpotri failed"};
     hipLaunchKernelGGL(symmetrize_kernel, dim3((unsigned)blocks_for(s * s)), dim3(kGS), 0, 0, Fd.p, s, f);
     SEM_HIP(hipGetLastError());
-    // Large node: forward [S^-1 ; W] row-major = column-major s x (s + b):
-    // [S^-1 | W^T].  Small node: forward [S^-1 ; W] column-major (ld s + b).
-    // Backward, every node: W^T row-major = W column-major (ld b).
+    // forward [S^-1 ; W] by rows = column-major s x (s + b) [S^-1 | W^T];
+    // backward W^T by rows = column-major W
     double* X = m->fwd_pool.p + F.fwd;
-    double* Wb = m->bwd_pool.p + F.bwd;
-    const int64_t ldx = F.small ? f : s;
-    SEM_HIP(hipMemcpy2D(X, ldx * sizeof(double), Fd.p, f * sizeof(double), s * sizeof(double), s,
-                        hipMemcpyDeviceToDevice));
+    double* W = m->bwd_pool.p + F.bwd;
+    const rocblas_int si = (rocblas_int)s, bi = (rocblas_int)b, fi = (rocblas_int)f;
+    SEM_HIP(hipMemcpy2DAsync(X, F.lds * sizeof(double), Fd.p, f * sizeof(double), s * sizeof(double), s,
+                             hipMemcpyDeviceToDevice, 0));
     if (b > 0) {
-      const rocblas_int si = (rocblas_int)s, bi = (rocblas_int)b, fi = (rocblas_int)f;
-      // W = F_BI S^-1  (b x s), column-major (ld b) for the backward sweep
-      double* W = Wb;
-      const rocblas_int ldw = bi;
-      if (rocblas_dgemm(hb, rocblas_operation_none, rocblas_operation_none, bi, si, si, &one, Fd.p + s, fi, Fd.p,
-                        fi, &zero, W, ldw) != rocblas_status_success)
+      // W = F_BI S^-1  (b x s), W^T = S^-1 F_IB  (s x b, the columns from s on)
+      if (rocblas_dgemm(hb, rocblas_operation_none, rocblas_operation_none, bi, si, si, &one, Fd.p + s, fi, Fd.p, fi,
+                        &zero, W, F.ldb) != rocblas_status_success)
         throw Error{SEM_EHIP, "rocblas_dgemm failed"};
-      if (F.small) {
-        // forward rows s.. of the column-major [S^-1; W]
-        SEM_HIP(hipMemcpy2D(X + s, f * sizeof(double), W, b * sizeof(double), b * sizeof(double), s,
-                            hipMemcpyDeviceToDevice));
-      } else {
-        // W^T = S^-1 F_IB  (s x b), the forward columns s..
-        if (rocblas_dgemm(hb, rocblas_operation_none, rocblas_operation_none, si, bi, si, &one, Fd.p, fi,
-                          Fd.p + s * f, fi, &zero, X + s * s, si) != rocblas_status_success)
-          throw Error{SEM_EHIP, "rocblas_dgemm failed"};
-      }
+      if (rocblas_dgemm(hb, rocblas_operation_none, rocblas_operation_none, si, bi, si, &one, Fd.p, fi, Fd.p + s * f,
+                        fi, &zero, X + s * F.lds, F.lds) != rocblas_status_success)
+        throw Error{SEM_EHIP, "rocblas_dgemm failed"};
       // U = F_BB - W F_IB, pushed for the parent
       if (top + b * b > std::max<int64_t>(T.ustack_size, 1)) throw Error{SEM_EHIP, "coarse update stack overflow"};
       double* U = Ust.p + top;
-      SEM_HIP(hipMemcpy2D(U, b * sizeof(double), Fd.p + s + s * f, f * sizeof(double), b * sizeof(double), b,
-                          hipMemcpyDeviceToDevice));
-      if (rocblas_dgemm(hb, rocblas_operation_none, rocblas_operation_none, bi, bi, si, &mone, W, ldw, Fd.p + s * f,
+      SEM_HIP(hipMemcpy2DAsync(U, b * sizeof(double), Fd.p + s + s * f, f * sizeof(double), b * sizeof(double), b,
+                               hipMemcpyDeviceToDevice, 0));
+      if (rocblas_dgemm(hb, rocblas_operation_none, rocblas_operation_none, bi, bi, si, &mone, W, F.ldb, Fd.p + s * f,
                         fi, &one, U, bi) != rocblas_status_success)
         throw Error{SEM_EHIP, "rocblas_dgemm failed"};
       u_at[q] = top;
       top += b * b;
     }
   }
+  std::vector<rocblas_int> bad(2 * nn);
+  SEM_HIP(hipMemcpy(bad.data(), info.p, bad.size() * sizeof(rocblas_int), hipMemcpyDeviceToHost));
+  for (rocblas_int v : bad)
+    if (v != 0) throw Error{SEM_EMESH, "coarse matrix is not positive definite"};
   SEM_HIP(hipDeviceSynchronize());
   build_coarse_graph(m);
 }
@@ -888,18 +851,6 @@ void upload_all(sem_mesh m) {
   m->einc_off.upload(T.einc_off.data(), T.einc_off.size());
   m->dir.upload(T.dir.data(), T.dir.size());
   m->fcount.upload(T.fcount.data(), T.fcount.size());
-  {
-    // vertex incidence -> element * 8 + corner
-    std::vector<int32_t> ec(T.vinc_off.back());
-    std::vector<int32_t> fill(T.vinc_off.begin(), T.vinc_off.end() - 1);
-    const int N = T.N;
-    for (int64_t e = 0; e < T.E; ++e)
-      for (int p = 0; p < 8; ++p) {
-        const int64_t v = gid_of(T, e, (p & 1) * N, ((p >> 1) & 1) * N, (p >> 2) * N);
-        ec[fill[v]++] = (int32_t)(e * 8 + p);
-      }
-    m->vinc_ec.upload(ec.data(), ec.size());
-  }
   m->G64.upload(T.G.data(), T.G.size());
   const std::vector<double> Dx = d_with_split(T.D, T.n1);
   m->D64.upload(Dx.data(), Dx.size());
@@ -942,7 +893,6 @@ void upload_all(sem_mesh m) {
     phi[T.n1 + i] = 0.5 * (1.0 + T.t[i]);
   }
   m->phi.upload(phi.data(), phi.size());
-  m->Re.alloc((size_t)T.E * 8);
   m->Zv.alloc(std::max<int64_t>(T.V, 1));
   m->part.alloc(kRedBlocks);
   m->sc.alloc(16);
@@ -1097,7 +1047,7 @@ int pcg_core(sem_mesh m, T* x, T* r, double bnorm2, double rr0, double rtol, int
   bool pending_x = false;  // x += alpha p of the last iteration not yet applied
   // two-scale P with a coarse space: the update of r also restricts it, and
   // the coarse solve starts beside the convergence check and the patch solves
-  const bool fused = pc == SEM_PC_TWOSCALE && m->T.nc > 0 && !m->direct_coarse;
+  const bool fused = pc == SEM_PC_TWOSCALE && m->T.nc > 0 && !m->in_capture;
   bool coarse_pending = false;
   // speculative ordering of the convergence check: needs the pinned read-back
   // buffer (made by an ordinary solve's set-up; not in the allocation-free one)
@@ -1633,8 +1583,8 @@ int sem_mesh_tile(sem_mesh m, int dtype, int* epb) {
 
 int sem_mesh_coarse_factor_size(sem_mesh m, int64_t* fwd_entries, int64_t* bwd_entries) {
   if (!m || !fwd_entries || !bwd_entries) return SEM_EINVAL;
-  *fwd_entries = m->T.fwd_size;
-  *bwd_entries = m->T.bwd_size;
+  *fwd_entries = m->T.fwd_entries;
+  *bwd_entries = m->T.bwd_entries;
   return SEM_OK;
 }
 
@@ -1897,8 +1847,9 @@ int sem_coarse_solve(sem_mesh m, const double* R, double* Z, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     const HostTables& T = m->T;
     if (T.nc > 0) {
-      hipLaunchKernelGGL(coarse_gather_vertex_kernel, dim3((unsigned)blocks_for(T.V)), dim3(kGS), 0, s, m->Rlev.p, R,
-                         m->cidx.p, T.V);
+      hipLaunchKernelGGL(coarse_set_rhs_kernel, dim3((unsigned)blocks_for(T.nc)), dim3(kGS), 0, s, m->cvec.p, R,
+                         (const int32_t*)m->rs_off.p, (const int32_t*)m->pslot.p, (const int32_t*)m->cvert.p,
+                         (const int32_t*)m->vinc_off.p, T.nc);
       SEM_HIP(hipGetLastError());
       coarse_solve_tree(m, s);
     } else {

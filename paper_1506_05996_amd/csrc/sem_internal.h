@@ -43,51 +43,75 @@ inline int32_t pack_coef(int ai, int aj, int ak) {
 // Coarse solve by nested dissection.  The free-vertex graph of each connected
 // component is split recursively by separators (one BFS level across the
 // longest extent); the separators and the final small parts are the nodes of
-// a forest, numbered in post-order, and each node's own vertices form one
-// contiguous range of coarse indices.  A node t holds its own vertices I and
-// the boundary B: the vertices of its ancestors coupled to its subtree once
-// the subtree is eliminated.  After elimination of the subtree, the front
-// [F_II F_IB; F_BI F_BB] gives S = F_II and W = F_BI S^-1.
-// Nodes with s <= kSmallFront are "small": their forward product runs one lane
-// per row (the forward matrix is stored transposed so that lanes read
-// consecutive rows); larger nodes, and every backward product, use one wave
-// per row.
-constexpr int kSmallFront = 128;
-
+// a forest, of which runs of consecutive heights are then merged into single
+// nodes (see merge_heights).  Nodes are numbered in post-order, and each node's
+// own vertices form one contiguous range of coarse indices.  A node t holds its
+// own vertices I and the boundary B: the vertices of its ancestors coupled to
+// its subtree once the subtree is eliminated.  After elimination of the
+// subtree, the front [F_II F_IB; F_BI F_BB] gives S = F_II and W = F_BI S^-1.
+//
+// Rows of the sweeps: node t owns the row slots roff .. roff + s + b - 1 (its
+// own vertices, then its boundary).  The values that a row starts from sit side
+// by side in the contribution vector, row slot g holding entries
+// rs_off[g] .. rs_off[g + 1]: for an own row the negated coarse residual at its
+// vertex, then one entry per child whose boundary holds the vertex; for a
+// boundary row the children's entries alone.  A child writes entry k of its
+// contribution straight to its parent's slot cdst[coff + k].  The residual
+// comes in parts, one per element at the vertex: they are the first entries of
+// a leaf's row, and of a higher row sit in a slot of their own (slots past the
+// row slots), whose sum the lowest launch writes to the row's first entry.
 struct FrontNode {
   int64_t off;     // first coarse index of the node's own vertices
-  int64_t fwd;     // offset of [S^-1 ; W] in the forward pool: (s + b) x s row-major,
-                   // or column-major (leading dimension s + b) for a small node
-  int64_t bwd;     // offset of W^T (s x b, row-major) in the backward pool
+  int64_t fwd;     // offset of [S^-1 ; W] in the forward pool: (s + b) rows of s, row stride lds
+  int64_t bwd;     // offset of W^T in the backward pool: s rows of b, row stride ldb
   int64_t bidx;    // offset of the boundary list (ascending coarse indices) in fb_idx
-  int64_t coff;    // offset of the node's contribution W y in the contribution vector
+  int64_t coff;    // offset of the node's contribution slots in cdst
+  int64_t roff;    // first row slot
   int32_t s;       // own vertices
   int32_t b;       // boundary vertices
+  int32_t lds, ldb;  // row strides: s and b rounded up to even, so that rows are 16-byte aligned
   int32_t parent;  // -1 for a root
   int32_t height;  // 0 for a leaf, else 1 + the largest height of its children
-  int32_t small;   // 1 when s <= kSmallFront
+};
+
+inline int32_t even_up(int32_t v) { return (v + 1) & ~1; }
+
+// one workgroup of a coarse sweep: rows row .. row + 4 RW - 1 of one node
+struct CoarseTile {
+  int64_t mat;   // the node's matrix in the forward or backward pool
+  int32_t ld;    // row stride
+  int32_t len;   // row length: s forward, b backward
+  int32_t row;   // first row
+  int32_t rows;  // rows of the node: s + b forward, s backward
+  int32_t s;     // own vertices
+  int32_t off;   // first coarse index
+  int32_t src;   // forward: first row slot; backward: offset of the boundary list
+  int32_t coff;  // forward: offset of the contribution slots
+  int32_t root;  // no boundary: the forward rows are the solution
   int32_t pad;
 };
 
-// Tile shape of the sweeps for a row length L: rows per wave (4 for short
-// rows, whose node vector serves four rows; 2 beyond 256) and, beyond 1024
-// columns, rows split across the workgroup's 4 waves (more waves in flight
-// for the long rows of the upper heights).  A tile holds rw rows when split,
-// else 4 rw.
-struct CoarseTileShape {
-  int32_t rw;
-  int32_t split;
-};
-inline CoarseTileShape coarse_tile_shape(int64_t L) {
-  if (L <= 256) return CoarseTileShape{4, 0};
-  return CoarseTileShape{2, L > 1024 ? 1 : 0};
+// Rows per wave of a sweep launch over `rows` rows of at most `len` entries.
+// Every workgroup stages its node's vector for its own rows, so more rows per
+// wave save staging, as long as enough waves are left to keep the chip's loads
+// in flight: at least 1,024 forward, where an entry of the vector is a sum of
+// several loads, and 2,048 backward, where it is one (24^3: 42.8 us with 1,024
+// and 2,048, 48 us with 4,096 for both; 56^3 488 against 498 us).  Rows of up to
+// 128 entries are one 16-byte load per lane, so eight of them fit the registers
+// that four longer rows take.
+inline int32_t coarse_rows_per_wave(int64_t rows, int64_t len, bool forward) {
+  const int64_t waves = forward ? 1024 : 2048;
+  const int32_t most = len <= 128 ? 8 : 4;
+  int32_t rw = 1;
+  while (rw < most && rows >= waves * rw * 2) rw *= 2;
+  return rw;
 }
-inline int32_t coarse_tile_rows(const CoarseTileShape& t) { return t.split ? t.rw : 4 * t.rw; }
 
-// one row of a per-height work list: (node, row or column of that node)
-struct RowItem {
-  int32_t node;
-  int32_t row;
+// one launch of a sweep: tiles [first, first + count) with rw rows per wave
+struct CoarseLaunch {
+  int64_t first, count;
+  int32_t rw;
+  int32_t wide;  // rows beyond 128 entries
 };
 
 struct HostTables {
@@ -143,20 +167,19 @@ struct HostTables {
   std::vector<FrontNode> fnodes;         // post-order
   std::vector<std::vector<int32_t>> fchildren;  // children of each node, ascending
   std::vector<int32_t> fb_idx;           // boundary lists
-  std::vector<int32_t> ct_off, ct_pos;   // [nc + 1]: contribution slots subtracted from each row
-  int64_t fwd_size = 0, bwd_size = 0, c_size = 0;
+  std::vector<int32_t> cvert;            // [nc] vertex of each coarse index
+  std::vector<int32_t> pslot;            // [nc] slot of the element parts of each coarse index
+  std::vector<int32_t> rs_off;           // [slots + 1]: entries of each slot
+  std::vector<int32_t> pre_slot, pre_row;  // part slots of the higher rows, and those rows
+  std::vector<int32_t> part_dst;         // [E][8]: entry of an element's part of the residual, -1 at Dirichlet vertices
+  std::vector<int32_t> cdst;             // [sum of b]: entry each contribution goes to
+  int64_t fwd_size = 0, bwd_size = 0;    // entries of the pools, padding included
+  int64_t fwd_entries = 0, bwd_entries = 0;  // without padding
+  int64_t c_size = 0;                    // entries of the contribution vector
   int64_t ustack_size = 0;               // largest sum of pending update matrices (set-up)
   int32_t max_front = 0;                 // largest s + b
-  int32_t n_heights = 0;
-  std::vector<int32_t> fy_off, fy_items;  // per height: coarse rows of large nodes to assemble
-  std::vector<int64_t> fr_off, br_off;    // per height: ranges of fr_items (large nodes) / br_items (all)
-  // forward tiles of large nodes (rows r.. of [S^-1; W], s + b rows per node) and
-  // backward tiles of every node (rows r.. of W^T, s per node): one workgroup
-  // per tile, the tile shape chosen per height
-  std::vector<RowItem> fr_items, br_items;
-  std::vector<CoarseTileShape> fr_shape, br_shape;  // per height: tile shape of the forward / backward launch
-  std::vector<int64_t> fs_off;            // per height: range of fs_items (small nodes)
-  std::vector<RowItem> fs_items;          // 64-row chunks of small nodes' forward rows
+  std::vector<CoarseTile> tiles;         // of all launches
+  std::vector<CoarseLaunch> fwd_launch, bwd_launch;  // in the order they run
   std::vector<double> corner_K;          // [E][8][8] order-1 element stiffness matrices
   std::vector<double> corner_M;          // [E][8] order-1 element mass (|J| at the corners, diagonal)
   std::vector<int64_t> coarse_vid;       // [E][8] global id of each element's corner vertices

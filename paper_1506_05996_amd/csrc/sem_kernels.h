@@ -1316,11 +1316,14 @@ schwarz_sum_kernel(T* __restrict__ z, T* __restrict__ w, const T* __restrict__ z
 }
 
 // Coarse restriction, per element: R_e[IJK] = sum over the nodes this element
-// owns of Phi_I(t_i) Phi_J(t_j) Phi_K(t_k) r_N  (= (I^T r) once gathered).
+// owns of Phi_I(t_i) Phi_J(t_j) Phi_K(t_k) r_N  (= (I^T r) once gathered).  The
+// eight parts go, negated, to the coarse rows' own entries of the contribution
+// vector (part_dst; -1: Dirichlet vertex), where the forward sweep sums them.
 template <int N, typename T>
 __global__ void __launch_bounds__((N + 1) * (N + 1))
-restrict_kernel(const T* __restrict__ r, double* __restrict__ Re, const int32_t* __restrict__ rec,
-                const double* __restrict__ phi, const int32_t* __restrict__ order, int64_t E) {
+restrict_kernel(const T* __restrict__ r, double* __restrict__ cvec, const int32_t* __restrict__ part_dst,
+                const int32_t* __restrict__ rec, const double* __restrict__ phi, const int32_t* __restrict__ order,
+                int64_t E) {
   constexpr int n1 = N + 1, P = n1 * n1;
   __shared__ double red[8][P + 1];  // padded: the eight summing lanes read eight distinct banks
   __shared__ double sPhi[2 * n1];
@@ -1369,21 +1372,21 @@ restrict_kernel(const T* __restrict__ r, double* __restrict__ Re, const int32_t*
       s3 += red[tid][x + 3];
     }
     for (; x < P; ++x) s0 += red[tid][x];
-    Re[e * 8 + tid] = (s0 + s1) + (s2 + s3);
+    const int32_t d = part_dst[e * 8 + tid];
+    if (d >= 0) cvec[d] = -((s0 + s1) + (s2 + s3));
   }
 }
 
 // r -= alpha w at the nodes each element owns (each global node once), with
 // the element's part of the coarse restriction of the updated r (as
-// restrict_kernel: Re[e][IJK] = sum over the owned nodes of
-// Phi_I(t_i) Phi_J(t_j) Phi_K(t_k) r_N) and of r . r (dpart[block], 0 for
-// the padding blocks).  Lets the coarse chain start right after the update
+// restrict_kernel) and of r . r (dpart[block], 0 for the padding blocks).  Lets the coarse chain start right after the update
 // of r, before the patch solves.
 template <int N, typename T>
 __global__ void __launch_bounds__((N + 1) * (N + 1))
 update_r_restrict_kernel(T* __restrict__ r, const T* __restrict__ w, const double* __restrict__ sc,
-                         double* __restrict__ Re, double* __restrict__ dpart, const int32_t* __restrict__ rec,
-                         const double* __restrict__ phi, const int32_t* __restrict__ order, int64_t E) {
+                         double* __restrict__ cvec, const int32_t* __restrict__ part_dst, double* __restrict__ dpart,
+                         const int32_t* __restrict__ rec, const double* __restrict__ phi,
+                         const int32_t* __restrict__ order, int64_t E) {
   constexpr int n1 = N + 1, P = n1 * n1;
   __shared__ double red[9][P + 1];  // padded rows: the summing lanes read distinct banks
   __shared__ double sPhi[2 * n1];
@@ -1438,234 +1441,244 @@ update_r_restrict_kernel(T* __restrict__ r, const T* __restrict__ w, const doubl
     }
     for (; x < P; ++x) s0 += red[tid][x];
     const double t = (s0 + s1) + (s2 + s3);
-    if (tid == 8)
+    if (tid == 8) {
       dpart[blockIdx.x] = t;
-    else if (valid)
-      Re[e * 8 + tid] = t;
+    } else if (valid) {
+      const int32_t d = part_dst[e * 8 + tid];
+      if (d >= 0) cvec[d] = -t;
+    }
   }
-}
-
-// coarse residual on the free vertices (coarse order): sum of the element parts
-__global__ void __launch_bounds__(256)
-restrict_gather_kernel(double* __restrict__ R, const double* __restrict__ Re, const int32_t* __restrict__ vinc_off,
-                       const int32_t* __restrict__ vinc_ec, const int32_t* __restrict__ cidx, int64_t V) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= V) return;
-  const int32_t c = cidx[v];
-  if (c < 0) return;
-  // four incidences in flight at a time; the sum still runs in list order
-  const int32_t q1 = vinc_off[v + 1];
-  int32_t q = vinc_off[v];
-  double s = 0.0;
-  for (; q + 4 <= q1; q += 4) {
-    const int32_t a0 = vinc_ec[q], a1 = vinc_ec[q + 1], a2 = vinc_ec[q + 2], a3 = vinc_ec[q + 3];
-    const double b0 = Re[a0], b1 = Re[a1], b2 = Re[a2], b3 = Re[a3];
-    s += b0;
-    s += b1;
-    s += b2;
-    s += b3;
-  }
-  for (; q < q1; ++q) s += Re[vinc_ec[q]];
-  R[c] = s;
 }
 
 // Nested-dissection solve of the coarse system, node by node in height order.
 //   forward, height h (leaves first), node t with own rows I and boundary B:
-//     y_I = R_I - (contributions W_d y_d of the descendants d with I in B_d)
-//     Z_I = S_t^-1 y_I,   c_t = W_t y_I        (one stacked product [S^-1; W] y)
+//     y_I = R_I - (the children's contributions to I)
+//     Z_I = S_t^-1 y_I,   c_t = W_t y_t + (the children's contributions to B)
 //   backward, height h (roots first):
 //     X_I = Z_I - W_t^T X_B
-// All rows are independent within a height; sums run in a fixed order.
-
-// y_i = R_i - sum of the contributions listed for row i: 8 lanes per row,
-// lane t taking every 8th entry from t, then a fixed shuffle tree
-__global__ void __launch_bounds__(256)
-coarse_assemble_kernel(double* __restrict__ Y, const double* __restrict__ R, const double* __restrict__ cvec,
-                       const int32_t* __restrict__ ct_off, const int32_t* __restrict__ ct_pos,
-                       const int32_t* __restrict__ items, int64_t n) {
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t x = gid >> 3;
-  const int sub = (int)(gid & 7);
-  if (x >= n) return;  // whole 8-lane groups leave together
-  const int32_t i = items[x];
-  double s = 0.0;
-  for (int32_t q = ct_off[i] + sub; q < ct_off[i + 1]; q += 8) s += cvec[ct_pos[q]];
-  s += __shfl_xor(s, 4, 8);
-  s += __shfl_xor(s, 2, 8);
-  s += __shfl_xor(s, 1, 8);
-  if (sub == 0) Y[i] = R[i] - s;
-}
+// c_t goes to the parent's rows, so a row sums one entry per child and not one
+// per descendant.  All rows are independent within a height; sums run in a
+// fixed order.
+//
+// One launch per height and direction; a workgroup takes 4 RW rows of one node
+// (wave w: rows row + w RW ..), each lane two consecutive columns at a time.
+// What bounds a launch of a small or middling mesh is latency, not bytes: the
+// matrix loads of a chunk are issued before the node's vector is assembled, so
+// that both are in flight together; the vector (the rows' entries forward, the
+// ancestors' solution backward) passes through LDS in chunks of kCoarseStage.
+// NARROW (rows of at most 128 entries): one load per row and lane.
+constexpr int kCoarseStage = 1024;
 
 __device__ __forceinline__ double wave_sum(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
 }
 
-// Tiled sweeps: one workgroup (4 waves) per tile of rows of one node.  Not
-// split: a tile of 4 RW consecutive rows, wave w taking rows r + w RW ..
-// r + w RW + RW - 1, each lane its columns c = lane + 64 j.  Split (rows
-// longer than 1024): a tile of RW rows shared by the 4 waves, wave w taking
-// the column blocks c = 64 w + lane + 256 j, the 4 partial sums of a row
-// added in wave order through LDS.  The vector the rows are dotted with (y_I
-// forward, x_B backward) passes through LDS in chunks of kCoarseStage entries
-// (a multiple of 256), each staged once per tile; sums run in ascending c
-// within a lane, then a wave sum per row.
-constexpr int kCoarseStage = 1024;
-
-// the wave's RW dot products against the staged vector; returns them summed over the wave (lane 0 holds them)
-template <int RW, bool SPLIT>
-__device__ __forceinline__ void coarse_tile_dots(const double* const (&rp)[RW], double (&acc)[RW], int len,
-                                                 const double* __restrict__ stage_src,
-                                                 const int32_t* __restrict__ gather_idx, double* sv) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cfirst = SPLIT ? 64 * wave + lane : lane, cstep = SPLIT ? 256 : 64;
-  for (int c0 = 0; c0 < len; c0 += kCoarseStage) {
-    const int cn = min(kCoarseStage, len - c0);
-    __syncthreads();  // the previous chunk is consumed
-    for (int c = threadIdx.x; c < cn; c += 256)
-      sv[c] = gather_idx != nullptr ? stage_src[gather_idx[c0 + c]] : stage_src[c0 + c];
-    __syncthreads();
-#pragma unroll 2
-    for (int c = cfirst; c < cn; c += cstep) {
-      const double vc = sv[c];
+// sums of the entries of the U row slots g[u] (negative: none) of the
+// contribution vector, each in order; all rows' loads go out together, W
+// entries of each at a time
+template <int U, int W>
+__device__ __forceinline__ void row_entries(const double* __restrict__ cvec, const int32_t* __restrict__ rs_off,
+                                            const int (&g)[U], double (&sum)[U]) {
+  int32_t q0[U], n[U], most = 0;
 #pragma unroll
-      for (int i = 0; i < RW; ++i) acc[i] += rp[i][c0 + c] * vc;
-    }
+  for (int u = 0; u < U; ++u) {
+    const int gu = max(g[u], 0);
+    q0[u] = rs_off[gu];
+    n[u] = rs_off[gu + 1];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    n[u] = g[u] >= 0 ? n[u] - q0[u] : 0;
+    most = max(most, n[u]);
+    sum[u] = 0.0;
+  }
+  for (int32_t q = 0; q < most; q += W) {
+    double v[U][W];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < W; ++i) v[u][i] = cvec[q0[u] + max(min(q + i, n[u] - 1), 0)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < W; ++i) sum[u] += q + i < n[u] ? v[u][i] : 0.0;
   }
 }
 
-// row sums of a tile: not split, each wave's own rows; split, the 4 waves'
-// partial sums of the shared rows in wave order (thread 0 holds them)
-template <int RW, bool SPLIT>
-__device__ __forceinline__ void coarse_tile_reduce(double (&acc)[RW], double (*sp)[RW]) {
-#pragma unroll
-  for (int i = 0; i < RW; ++i) acc[i] = wave_sum(acc[i]);
-  if constexpr (SPLIT) {
-    if ((threadIdx.x & 63) == 0)
-#pragma unroll
-      for (int i = 0; i < RW; ++i) sp[threadIdx.x >> 6][i] = acc[i];
-    __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-      for (int i = 0; i < RW; ++i) acc[i] = ((sp[0][i] + sp[1][i]) + sp[2][i]) + sp[3][i];
-  }
-}
-
-// forward, large nodes: rows of [S^-1; W] (row-major, s columns); rows < s
-// give Z, the others the node's contribution
-template <int RW, bool SPLIT>
-__global__ void __launch_bounds__(256)
-coarse_fwd_kernel(double* __restrict__ Z, double* __restrict__ cvec, const double* __restrict__ Y,
-                  const double* __restrict__ pool, const FrontNode* __restrict__ nodes,
-                  const RowItem* __restrict__ tiles) {
-  __shared__ double sv[kCoarseStage];
-  __shared__ double sp[4][RW];
-  const RowItem ti = tiles[blockIdx.x];
-  const FrontNode nd = nodes[ti.node];
-  const int s = nd.s, f = nd.s + nd.b;
-  const int r0 = SPLIT ? ti.row : ti.row + (threadIdx.x >> 6) * RW;
-  const double* rp[RW];
-  double acc[RW];
-#pragma unroll
-  for (int i = 0; i < RW; ++i) {
-    rp[i] = pool + nd.fwd + (int64_t)min(r0 + i, f - 1) * s;  // rows past the node: read, not stored
-    acc[i] = 0.0;
-  }
-  coarse_tile_dots<RW, SPLIT>(rp, acc, s, Y + nd.off, nullptr, sv);
-  coarse_tile_reduce<RW, SPLIT>(acc, sp);
-  if (SPLIT ? threadIdx.x == 0 : (threadIdx.x & 63) == 0)
-#pragma unroll
-    for (int i = 0; i < RW; ++i) {
-      const int r = r0 + i;
-      if (r >= f) break;
-      if (r < s)
-        Z[nd.off + r] = acc[i];
-      else
-        cvec[nd.coff + r - s] = acc[i];
-    }
-}
-
-// value of v held by lane l (l wave-uniform)
-__device__ __forceinline__ double lane_value(double v, int l) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l), hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// small nodes (s <= 128): one lane per row of [S^-1; W] (column-major,
-// leading dimension s + b), 64-row chunks; y sits in two registers per lane
-// and is broadcast with readlane; matrix loads go out eight at a time.  Each
-// wave assembles the node's y itself (lane i: y_i = R_i minus the listed
-// contributions of the descendants, in list order), so heights with only
-// small nodes need no assembly launch.
-__global__ void __launch_bounds__(256)
-coarse_fwd_small_kernel(double* __restrict__ Z, double* __restrict__ cvec, const double* __restrict__ R,
-                        const int32_t* __restrict__ ct_off, const int32_t* __restrict__ ct_pos,
-                        const double* __restrict__ pool, const FrontNode* __restrict__ nodes,
-                        const RowItem* __restrict__ items, int64_t n) {
-  const int64_t it = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+// sums over the wave of RW values per lane in a fixed tree: the rows are dealt
+// to parts of the wave while lanes are added, so that lanes l with
+// l % (64 / RW) == 0 end with the sum of row l / (64 / RW)
+template <int RW>
+__device__ __forceinline__ double wave_rows_sum(double (&a)[RW]) {
   const int lane = threadIdx.x & 63;
-  if (it >= n) return;  // whole wave
-  const RowItem ri = items[it];
-  const FrontNode nd = nodes[ri.node];
-  const int f = nd.s + nd.b, s = nd.s;
-  const int rho = ri.row * 64 + lane;
-  const int rr = rho < f ? rho : f - 1;
-  const double* M = pool + nd.fwd + rr;
-  auto y_row = [&](int64_t g) {  // assembled y of coarse row g (contributions written by earlier launches)
-    double a = 0.0;
-    for (int32_t q = ct_off[g]; q < ct_off[g + 1]; ++q) a += cvec[ct_pos[q]];
-    return R[g] - a;
-  };
-  const double y0 = lane < s ? y_row(nd.off + lane) : 0.0;
-  const double y1 = lane + 64 < s ? y_row(nd.off + lane + 64) : 0.0;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int c0 = 0; c0 < s; c0 += 8) {
-    double mv[8];
+  if constexpr (RW == 1) {
+    return wave_sum(a[0]);
+  } else {
+    const bool hi = (lane & 32) != 0;
+    double v[RW / 2];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) mv[u] = M[(int64_t)(c0 + u < s ? c0 + u : s - 1) * f];
+    for (int i = 0; i < RW / 2; ++i) {
+      const double keep = hi ? a[i + RW / 2] : a[i], give = hi ? a[i] : a[i + RW / 2];
+      v[i] = keep + __shfl_xor(give, 32);
+    }
+    if constexpr (RW == 2) {
+      double s = v[0];
+      for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      return s;
+    } else {
+      const bool hi2 = (lane & 16) != 0;
+      double w[RW / 4];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int c = c0 + u;
-      if (c < s) acc[u & 3] += mv[u] * lane_value(c < 64 ? y0 : y1, c & 63);
+      for (int i = 0; i < RW / 4; ++i) {
+        const double keep = hi2 ? v[i + RW / 4] : v[i], give = hi2 ? v[i] : v[i + RW / 4];
+        w[i] = keep + __shfl_xor(give, 16);
+      }
+      if constexpr (RW == 4) {
+        double s = w[0];
+        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        return s;
+      } else {
+        const bool hi3 = (lane & 8) != 0;
+        double s = (hi3 ? w[1] : w[0]) + __shfl_xor(hi3 ? w[0] : w[1], 8);
+        for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        return s;
+      }
     }
   }
-  const double v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  if (rho < s)
-    Z[nd.off + rho] = v;
-  else if (rho < f)
-    cvec[nd.coff + rho - s] = v;
 }
 
-// backward: rows of W^T (row-major, b columns), one per own column c of a
-// node: X_c = Z_c - (W^T)_c . X_B (X_B final from the ancestors' launches)
-template <int RW, bool SPLIT>
-__global__ void __launch_bounds__(256)
-coarse_bwd_kernel(double* __restrict__ X, const double* __restrict__ Z, const double* __restrict__ pool,
-                  const int32_t* __restrict__ fb_idx, const FrontNode* __restrict__ nodes,
-                  const RowItem* __restrict__ tiles) {
-  __shared__ double sv[kCoarseStage];
-  __shared__ double sp[4][RW];
-  const RowItem ti = tiles[blockIdx.x];
-  const FrontNode nd = nodes[ti.node];
-  const int s = nd.s, b = nd.b;
-  const int r0 = SPLIT ? ti.row : ti.row + (threadIdx.x >> 6) * RW;
+// the wave's RW dot products (rows r0 .. of the tile's matrix) against the
+// node's vector, entries c + 256 u given by vec(c, end, v[U]); partial sums per lane in acc
+template <int RW, bool NARROW, typename Vec>
+__device__ __forceinline__ void coarse_tile_dots(const CoarseTile& t, const double* __restrict__ pool, int r0,
+                                                 double* sv, double (&acc)[RW], Vec vec) {
+  constexpr int NJ = NARROW ? 1 : 4;  // 16-byte loads per row and lane ahead of the vector
+  const int lane = threadIdx.x & 63;
   const double* rp[RW];
-  double acc[RW];
 #pragma unroll
   for (int i = 0; i < RW; ++i) {
-    rp[i] = pool + nd.bwd + (int64_t)min(r0 + i, s - 1) * b;
+    rp[i] = pool + t.mat + (int64_t)min(r0 + i, t.rows - 1) * t.ld;  // rows past the node: read, not stored
     acc[i] = 0.0;
   }
-  coarse_tile_dots<RW, SPLIT>(rp, acc, b, X, fb_idx + nd.bidx, sv);
-  coarse_tile_reduce<RW, SPLIT>(acc, sp);
-  if (SPLIT ? threadIdx.x == 0 : (threadIdx.x & 63) == 0)
+  for (int c0 = 0; c0 < t.len; c0 += kCoarseStage) {
+    const int cn = min(kCoarseStage, t.len - c0);
+    double2 mv[RW][NJ];
 #pragma unroll
-    for (int i = 0; i < RW; ++i) {
-      const int r = r0 + i;
-      if (r >= s) break;
-      X[nd.off + r] = Z[nd.off + r] - acc[i];
+    for (int j = 0; j < NJ; ++j) {
+      const int c = 2 * lane + 128 * j;
+#pragma unroll
+      for (int i = 0; i < RW; ++i)
+        mv[i][j] = c < cn ? *reinterpret_cast<const double2*>(rp[i] + c0 + c) : make_double2(0.0, 0.0);
     }
+    if (c0 > 0) __syncthreads();  // the previous chunk is consumed
+    {  // entries past the end are 0 (the padding of an odd row meets one)
+      double v[NJ];
+      vec(c0 + (int)threadIdx.x, c0 + cn, v);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        if (!NARROW || threadIdx.x < 128) sv[threadIdx.x + 256 * j] = v[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int c = 2 * lane + 128 * j;
+      if (c < cn) {
+        const double2 v = *reinterpret_cast<const double2*>(sv + c);
+#pragma unroll
+        for (int i = 0; i < RW; ++i) acc[i] += mv[i][j].x * v.x + mv[i][j].y * v.y;
+      }
+    }
+    if constexpr (!NARROW) {
+#pragma unroll 2
+      for (int c = 2 * lane + 128 * NJ; c < cn; c += 128) {
+        const double2 v = *reinterpret_cast<const double2*>(sv + c);
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+          const double2 m = *reinterpret_cast<const double2*>(rp[i] + c0 + c);
+          acc[i] += m.x * v.x + m.y * v.y;
+        }
+      }
+    }
+  }
+}
+
+// forward: rows of [S^-1; W]; rows < s give Z (in X; final, with the vertex
+// values, where the node has no boundary), the others the node's contribution.
+// The lowest launch has further workgroups (from n_tiles on) that sum the
+// element parts of the rows of all higher nodes into those rows' first
+// entries, so that the tiles above, each of which assembles its whole node,
+// read one entry instead of eight.
+template <int RW, bool NARROW>
+__global__ void __launch_bounds__(256)
+coarse_fwd_kernel(double* __restrict__ X, double* __restrict__ Zv, double* __restrict__ cvec,
+                  const double* __restrict__ pool, const CoarseTile* __restrict__ tiles,
+                  const int32_t* __restrict__ rs_off, const int32_t* __restrict__ cdst,
+                  const int32_t* __restrict__ cvert, int n_tiles, const int32_t* __restrict__ pre_slot,
+                  const int32_t* __restrict__ pre_row, int n_pre) {
+  __shared__ __attribute__((aligned(16))) double sv[NARROW ? 128 : kCoarseStage];
+  if ((int)blockIdx.x >= n_tiles) {
+    const int x = ((int)blockIdx.x - n_tiles) * 256 + (int)threadIdx.x;
+    if (x >= n_pre) return;
+    const int g[1] = {pre_slot[x]};
+    double v[1];
+    row_entries<1, 8>(cvec, rs_off, g, v);
+    cvec[rs_off[pre_row[x]]] = v[0];
+    return;
+  }
+  const CoarseTile t = tiles[blockIdx.x];
+  const int lane = threadIdx.x & 63, r0 = t.row + (threadIdx.x >> 6) * RW;
+  double acc[RW];
+  coarse_tile_dots<RW, NARROW>(t, pool, r0, sv, acc, [&](int c, int end, auto& v) {
+    constexpr int U = NARROW ? 1 : 4;
+    int g[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) g[u] = c + 256 * u < end ? t.src + c + 256 * u : -1;
+    row_entries<U, NARROW ? 8 : 4>(cvec, rs_off, g, v);
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = -v[u];
+  });
+  const double v = wave_rows_sum<RW>(acc);
+  const int r = r0 + lane / (64 / RW);
+  if (lane % (64 / RW) != 0 || r >= t.rows) return;
+  if (r < t.s) {
+    X[t.off + r] = v;
+    if (t.root) Zv[cvert[t.off + r]] = v;
+  } else {
+    const int g[1] = {t.src + r};
+    double c[1];
+    row_entries<1, 4>(cvec, rs_off, g, c);
+    cvec[cdst[t.coff + r - t.s]] = v + c[0];
+  }
+}
+
+// backward: rows of W^T, one per own vertex c of a node: X_c = Z_c - (W^T)_c . X_B
+// (X_B final from the ancestors' launches), also to the vertex values
+template <int RW, bool NARROW>
+__global__ void __launch_bounds__(256)
+coarse_bwd_kernel(double* __restrict__ X, double* __restrict__ Zv, const double* __restrict__ pool,
+                  const CoarseTile* __restrict__ tiles, const int32_t* __restrict__ fb_idx,
+                  const int32_t* __restrict__ cvert) {
+  __shared__ __attribute__((aligned(16))) double sv[NARROW ? 128 : kCoarseStage];
+  const CoarseTile t = tiles[blockIdx.x];
+  const int lane = threadIdx.x & 63, r0 = t.row + (threadIdx.x >> 6) * RW;
+  double acc[RW];
+  coarse_tile_dots<RW, NARROW>(t, pool, r0, sv, acc, [&](int c, int end, auto& v) {
+    constexpr int U = NARROW ? 1 : 4;
+    int32_t x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = fb_idx[t.src + min(c + 256 * u, end - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = X[x[u]];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = c + 256 * u < end ? v[u] : 0.0;
+  });
+  const double v = wave_rows_sum<RW>(acc);
+  const int r = r0 + lane / (64 / RW);
+  if (lane % (64 / RW) != 0 || r >= t.rows) return;
+  const double x = X[t.off + r] - v;
+  X[t.off + r] = x;
+  Zv[cvert[t.off + r]] = x;
 }
 
 // ---------------------------------------------------------------------------
@@ -1790,11 +1803,18 @@ amg_gemv_kernel(double* __restrict__ x, const double* __restrict__ Ainv, const d
   if (lane == 0) x[row] = acc;
 }
 
-// level-0 right-hand side from the coarse residual (nested-dissection order)
+// level-0 right-hand side: the element parts of the coarse residual at each
+// free vertex (the first entries of its part slot, negated there)
 __global__ void __launch_bounds__(256)
-amg_in_kernel(double* __restrict__ B0, const double* __restrict__ R, const int32_t* __restrict__ nd_of, int64_t n) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < n) B0[q] = R[nd_of[q]];
+amg_in_kernel(double* __restrict__ B0, const double* __restrict__ cvec, const int32_t* __restrict__ rs_off,
+              const int32_t* __restrict__ pslot, const int32_t* __restrict__ cvert,
+              const int32_t* __restrict__ vinc_off, const int32_t* __restrict__ nd_of, int64_t n) {
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (x >= n) return;
+  const int32_t c = nd_of[x], v = cvert[c], q0 = rs_off[pslot[c]];
+  double s = 0.0;
+  for (int32_t q = 0; q < vinc_off[v + 1] - vinc_off[v]; ++q) s += cvec[q0 + q];
+  B0[x] = -s;
 }
 
 // vertex-indexed result (0 on Dirichlet vertices) from the level-0 solution
@@ -1807,23 +1827,16 @@ amg_out_kernel(double* __restrict__ Zv, const double* __restrict__ X0, const int
   Zv[v] = c >= 0 ? X0[pos[c]] : 0.0;
 }
 
-// vertex-indexed coarse solution (0 on Dirichlet vertices)
+// a given coarse residual (vertex order) in place of the element parts: the
+// whole value as the first element's part, zeros as the others'
 __global__ void __launch_bounds__(256)
-coarse_scatter_kernel(double* __restrict__ Zv, const double* __restrict__ X, const int32_t* __restrict__ cidx,
-                      int64_t V) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= V) return;
-  const int32_t c = cidx[v];
-  Zv[v] = c >= 0 ? X[c] : 0.0;
-}
-
-__global__ void __launch_bounds__(256)
-coarse_gather_vertex_kernel(double* __restrict__ Rlev, const double* __restrict__ Rv, const int32_t* __restrict__ cidx,
-                            int64_t V) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= V) return;
-  const int32_t c = cidx[v];
-  if (c >= 0) Rlev[c] = Rv[v];
+coarse_set_rhs_kernel(double* __restrict__ cvec, const double* __restrict__ Rv, const int32_t* __restrict__ rs_off,
+                      const int32_t* __restrict__ pslot, const int32_t* __restrict__ cvert,
+                      const int32_t* __restrict__ vinc_off, int64_t nc) {
+  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= nc) return;
+  const int32_t v = cvert[c], q0 = rs_off[pslot[c]];
+  for (int32_t q = 0; q < vinc_off[v + 1] - vinc_off[v]; ++q) cvec[q0 + q] = q == 0 ? -Rv[v] : 0.0;
 }
 
 // --- set-up of the coarse fronts (column-major f x f front F, leading dimension f)
@@ -1833,6 +1846,13 @@ __global__ void symmetrize_kernel(double* __restrict__ A, int64_t n, int64_t ld)
   if (x >= n * n) return;
   const int64_t r = x % n, c = x / n;
   if (r < c) A[r + c * ld] = A[c + r * ld];
+}
+
+// entries of A_c into the zeroed front
+__global__ void front_scatter_kernel(double* __restrict__ F, const int32_t* __restrict__ pos,
+                                     const double* __restrict__ val, int64_t n) {
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (x < n) F[pos[x]] = val[x];
 }
 
 // F_IB = F_BI^T: F[c, s + k] = F[s + k, c] for c < s, k < b

@@ -1006,6 +1006,127 @@ void build_coarse_matrices(HostTables& T, const double* vtx, const int64_t* hex)
   });
 }
 
+// node of the dissection forest while it is built (parents before children)
+struct TNode {
+  std::vector<int64_t> own;
+  int32_t parent;
+  std::vector<int32_t> children;
+};
+
+static std::vector<int32_t> post_order(const std::vector<TNode>& nodes) {
+  std::vector<int32_t> post;
+  post.reserve(nodes.size());
+  std::vector<std::pair<int32_t, size_t>> st;
+  for (int32_t r = 0; r < (int32_t)nodes.size(); ++r) {
+    if (nodes[r].parent >= 0) continue;
+    st.push_back({r, 0});
+    while (!st.empty()) {
+      auto& top = st.back();
+      if (top.second < nodes[top.first].children.size()) {
+        const int32_t c = nodes[top.first].children[top.second++];
+        st.push_back({c, 0});
+      } else {
+        post.push_back(top.first);
+        st.pop_back();
+      }
+    }
+  }
+  return post;
+}
+
+// Merge runs of consecutive heights of the dissection forest.  A height costs
+// one forward and one backward launch, about 11 us in all however little it
+// reads, and middling fronts stream at about 2.6 TB/s, so a height is worth some
+// 3.5 M entries (measured on the meshes below with 2, 3.5, 4.8 and 7 M: 32^3 91,
+// 78, 78, 78 us; 40^3 175, 170, 174, 172 us; 10 x 10 x 125 32, 32, 32, 39 us).  Merging the heights a..b turns every connected piece of the
+// forest between them into one node (its own vertices those of the piece, its
+// boundary that of the piece's top): a denser S^-1, but one launch each way
+// instead of b - a + 1.  The cheapest partition of the heights into runs is
+// found exactly (shortest path over the run ends).  The exact
+// coarse solve alone, before and after, with the sweeps' kernels: 12^3 hexahedra
+// 65 -> 16 us (4 heights, one dense inverse), 24^3 149 -> 43 us (7 heights of
+// 54 MB, 3 of 69 MB), 23 x 29 x 31 141 -> 57 us, 40^3 262 -> 170 us (10 heights
+// of 398 MB, 7 of 438 MB), 56^3 541 -> 490 us (unmerged).
+static void merge_heights(std::vector<TNode>& nodes, const std::vector<std::vector<int64_t>>& adj, int64_t V) {
+  constexpr double kHeightEntries = 3.5e6;
+  constexpr int64_t kMaxMerged = 8192;  // rows of a merged front (factored densely)
+  const int32_t nn = (int32_t)nodes.size();
+  if (nn < 2) return;
+  const std::vector<int32_t> post = post_order(nodes);
+  std::vector<int32_t> order_of(V, -1), height(nn, 0), b(nn, 0);
+  std::vector<int64_t> end(nn, 0);
+  {  // symbolic elimination in post-order: heights and boundary sizes
+    int64_t next = 0;
+    for (int32_t t : post) {
+      for (int64_t v : nodes[t].own) order_of[v] = (int32_t)next++;
+      end[t] = next;
+    }
+    std::vector<std::vector<int32_t>> bnd(nn);
+    for (int32_t t : post) {
+      std::vector<int32_t> u;
+      for (int64_t v : nodes[t].own)
+        for (int64_t w : adj[v])
+          if (order_of[w] >= end[t]) u.push_back(order_of[w]);
+      for (int32_t c : nodes[t].children) {
+        for (int32_t g : bnd[c])
+          if (g >= end[t]) u.push_back(g);
+        height[t] = std::max(height[t], height[c] + 1);
+        std::vector<int32_t>().swap(bnd[c]);
+      }
+      std::sort(u.begin(), u.end());
+      u.erase(std::unique(u.begin(), u.end()), u.end());
+      b[t] = (int32_t)u.size();
+      bnd[t] = std::move(u);
+    }
+  }
+  const int32_t H = *std::max_element(height.begin(), height.end()) + 1;
+  // top of the piece that holds node t when the heights lo..hi are merged
+  auto tops = [&](int32_t lo, int32_t hi, std::vector<int32_t>& top) {
+    for (int32_t t = 0; t < nn; ++t) {  // parents before children
+      if (height[t] < lo || height[t] > hi) continue;
+      const int32_t p = nodes[t].parent;
+      top[t] = p >= 0 && height[p] <= hi ? top[p] : t;
+    }
+  };
+  std::vector<double> best(H + 1, 1e300);
+  std::vector<int32_t> from(H + 1, 0), top(nn, 0);
+  std::vector<int64_t> s(nn);
+  best[0] = 0.0;
+  for (int32_t lo = 0; lo < H; ++lo)
+    for (int32_t hi = lo; hi < H; ++hi) {
+      tops(lo, hi, top);
+      std::fill(s.begin(), s.end(), 0);
+      for (int32_t t = 0; t < nn; ++t)
+        if (height[t] >= lo && height[t] <= hi) s[top[t]] += (int64_t)nodes[t].own.size();
+      double cost = best[lo] + kHeightEntries;
+      bool fits = true;
+      for (int32_t t = 0; t < nn; ++t) {
+        if (s[t] == 0) continue;
+        cost += (double)s[t] * (double)(s[t] + 2 * (int64_t)b[t]);
+        fits = fits && (hi == lo || s[t] + b[t] <= kMaxMerged);
+      }
+      if (fits && cost < best[hi + 1]) {
+        best[hi + 1] = cost;
+        from[hi + 1] = lo;
+      }
+    }
+  for (int32_t e = H; e > 0; e = from[e]) tops(from[e], e - 1, top);
+  std::vector<int32_t> id(nn, -1);
+  std::vector<TNode> merged;
+  for (int32_t t = 0; t < nn; ++t) {
+    if (top[t] == t) {
+      const int32_t p = nodes[t].parent;
+      id[t] = (int32_t)merged.size();
+      merged.push_back(TNode{{}, p >= 0 ? id[top[p]] : -1, {}});
+      if (merged.back().parent >= 0) merged[merged.back().parent].children.push_back(id[t]);
+    }
+    std::vector<int64_t>& own = merged[id[top[t]]].own;
+    own.insert(own.end(), nodes[t].own.begin(), nodes[t].own.end());
+  }
+  for (TNode& m : merged) std::sort(m.own.begin(), m.own.end());
+  nodes.swap(merged);
+}
+
 void build_coarse_tree(HostTables& T, int leaf_max) {
   const int N = T.N;
   const int64_t E = T.E, V = T.V;
@@ -1044,11 +1165,6 @@ void build_coarse_tree(HostTables& T, int leaf_max) {
   auto coord = [&](int64_t v, int r) { return T.xN[v * 3 + r]; };
 
   // --- recursive dissection (explicit task stack; nodes created in pre-order)
-  struct TNode {
-    std::vector<int64_t> own;
-    int32_t parent;
-    std::vector<int32_t> children;
-  };
   std::vector<TNode> nodes;
   struct Task {
     std::vector<int64_t> verts;
@@ -1176,30 +1292,15 @@ void build_coarse_tree(HostTables& T, int leaf_max) {
     tasks.push_back(std::move(left));
   }
 
+  merge_heights(nodes, adj, V);
+
   // --- post-order numbering
   const int32_t nn = (int32_t)nodes.size();
-  std::vector<int32_t> post;
-  post.reserve(nn);
-  {
-    std::vector<std::pair<int32_t, size_t>> st;
-    for (int32_t r = 0; r < nn; ++r) {
-      if (nodes[r].parent >= 0) continue;
-      st.push_back({r, 0});
-      while (!st.empty()) {
-        auto& top = st.back();
-        if (top.second < nodes[top.first].children.size()) {
-          const int32_t c = nodes[top.first].children[top.second++];
-          st.push_back({c, 0});
-        } else {
-          post.push_back(top.first);
-          st.pop_back();
-        }
-      }
-    }
-  }
+  const std::vector<int32_t> post = post_order(nodes);
   std::vector<int32_t> rank(nn);
   for (int32_t q = 0; q < nn; ++q) rank[post[q]] = q;
   T.cidx.assign(V, -1);
+  T.cvert.clear();
   T.fnodes.assign(nn, FrontNode{});
   T.fchildren.assign(nn, {});
   int64_t nc = 0;
@@ -1209,7 +1310,10 @@ void build_coarse_tree(HostTables& T, int leaf_max) {
     F.off = nc;
     F.s = (int32_t)tn.own.size();
     F.parent = tn.parent >= 0 ? rank[tn.parent] : -1;
-    for (int64_t v : tn.own) T.cidx[v] = (int32_t)nc++;
+    for (int64_t v : tn.own) {
+      T.cidx[v] = (int32_t)nc++;
+      T.cvert.push_back((int32_t)v);
+    }
     for (int32_t c : tn.children) T.fchildren[q].push_back(rank[c]);
     std::sort(T.fchildren[q].begin(), T.fchildren[q].end());
   }
@@ -1238,86 +1342,125 @@ void build_coarse_tree(HostTables& T, int leaf_max) {
     maxh = std::max(maxh, h);
     bnd[q] = std::move(u);
   }
-  // every boundary vertex belongs to an ancestor (the separator property)
-  for (int32_t q = 0; q < nn; ++q) {
-    for (int32_t g : bnd[q]) {
-      int32_t a = T.fnodes[q].parent;
-      while (a >= 0 && !(g >= T.fnodes[a].off && g < T.fnodes[a].off + T.fnodes[a].s)) a = T.fnodes[a].parent;
-      if (a < 0) throw Error{SEM_EMESH, "coarse dissection: boundary vertex outside the ancestors"};
-    }
-  }
-  // --- offsets, contribution lists, per-height work lists, set-up sizes
+  // --- offsets, set-up sizes
   T.fb_idx.clear();
-  int64_t fwd = 0, bwd = 0, coff = 0;
+  T.pslot.assign(nc, 0);
+  T.pre_slot.clear();
+  T.pre_row.clear();
+  T.fwd_entries = T.bwd_entries = 0;
+  int64_t fwd = 0, bwd = 0, coff = 0, roff = 0;
   int32_t mf = 0;
   for (int32_t q = 0; q < nn; ++q) {
     FrontNode& F = T.fnodes[q];
     F.bidx = (int64_t)T.fb_idx.size();
     T.fb_idx.insert(T.fb_idx.end(), bnd[q].begin(), bnd[q].end());
+    F.lds = even_up(F.s);
+    F.ldb = even_up(F.b);
     F.fwd = fwd;
     F.bwd = bwd;
     F.coff = coff;
-    F.small = F.s <= kSmallFront ? 1 : 0;
-    fwd += (int64_t)(F.s + F.b) * F.s;
-    bwd += (int64_t)F.s * F.b;
+    F.roff = roff;
+    fwd += (int64_t)(F.s + F.b) * F.lds;
+    bwd += (int64_t)F.s * F.ldb;
+    T.fwd_entries += (int64_t)(F.s + F.b) * F.s;
+    T.bwd_entries += (int64_t)F.s * F.b;
     coff += F.b;
+    roff += F.s + F.b;
     mf = std::max(mf, F.s + F.b);
   }
   T.fwd_size = fwd;
   T.bwd_size = bwd;
-  T.c_size = coff;
   T.max_front = mf;
-  T.ct_off.assign(nc + 1, 0);
-  for (int32_t q = 0; q < nn; ++q)
-    for (int32_t g : bnd[q]) T.ct_off[g + 1]++;
-  for (int64_t r = 0; r < nc; ++r) T.ct_off[r + 1] += T.ct_off[r];
-  T.ct_pos.assign(T.ct_off[nc], 0);
+  // --- slots: element parts (ascending element and corner) in a leaf's rows
+  // or in the part slots after all rows, then the children's contributions
+  // (ascending child)
+  for (int32_t q = 0; q < nn; ++q) {
+    const FrontNode& F = T.fnodes[q];
+    for (int32_t r = 0; r < F.s; ++r) {
+      if (F.height == 0) {
+        T.pslot[F.off + r] = (int32_t)(F.roff + r);
+        continue;
+      }
+      T.pslot[F.off + r] = (int32_t)(roff + (int64_t)T.pre_slot.size());
+      T.pre_slot.push_back(T.pslot[F.off + r]);
+      T.pre_row.push_back((int32_t)(F.roff + r));
+    }
+  }
+  const int64_t slots = roff + (int64_t)T.pre_slot.size();
+  T.rs_off.assign(slots + 1, 0);
+  for (int32_t g : T.pre_row) T.rs_off[g + 1]++;
+  for (int64_t x = 0; x < E * 8; ++x)
+    if (T.cidx[vid[x]] >= 0) T.rs_off[T.pslot[T.cidx[vid[x]]] + 1]++;
+  std::vector<int32_t> target(coff);  // row slot each contribution goes to
+  for (int32_t q = 0; q < nn; ++q) {
+    const FrontNode& F = T.fnodes[q];
+    if (F.b == 0) continue;
+    if (F.parent < 0) throw Error{SEM_EMESH, "coarse dissection: boundary vertex outside the ancestors"};
+    const FrontNode& P = T.fnodes[F.parent];
+    const std::vector<int32_t>& pb = bnd[F.parent];
+    for (int32_t k = 0; k < F.b; ++k) {
+      const int32_t g = bnd[q][k];
+      int64_t row;
+      if (g >= P.off && g < P.off + P.s) {
+        row = g - P.off;
+      } else {  // every boundary vertex belongs to an ancestor (the separator property)
+        auto it = std::lower_bound(pb.begin(), pb.end(), g);
+        if (it == pb.end() || *it != g) throw Error{SEM_EMESH, "coarse dissection: boundary vertex outside the ancestors"};
+        row = P.s + (it - pb.begin());
+      }
+      target[F.coff + k] = (int32_t)(P.roff + row);
+      T.rs_off[P.roff + row + 1]++;
+    }
+  }
+  if (E * 8 + coff + nc >= (int64_t)INT32_MAX) throw Error{SEM_EUNSUPPORTED, "coarse contribution vector too large"};
+  for (int64_t g = 0; g < slots; ++g) T.rs_off[g + 1] += T.rs_off[g];
+  T.c_size = T.rs_off[slots];
   {
-    std::vector<int32_t> fill(T.ct_off.begin(), T.ct_off.end() - 1);
-    for (int32_t q = 0; q < nn; ++q)  // ascending node: fixed subtraction order
-      for (int32_t k = 0; k < T.fnodes[q].b; ++k)
-        T.ct_pos[fill[bnd[q][k]]++] = (int32_t)(T.fnodes[q].coff + k);
+    std::vector<int32_t> fill(T.rs_off.begin(), T.rs_off.end() - 1);
+    for (int32_t g : T.pre_row) fill[g]++;  // the first entry is the parts' sum
+    T.part_dst.assign(E * 8, -1);
+    for (int64_t x = 0; x < E * 8; ++x)
+      if (T.cidx[vid[x]] >= 0) T.part_dst[x] = fill[T.pslot[T.cidx[vid[x]]]]++;
+    T.cdst.assign(coff, 0);
+    for (int64_t x = 0; x < coff; ++x) T.cdst[x] = fill[target[x]]++;
   }
-  T.n_heights = maxh + 1;
-  T.fy_off.assign(T.n_heights + 1, 0);
-  T.fr_off.assign(T.n_heights + 1, 0);
-  T.br_off.assign(T.n_heights + 1, 0);
-  T.fs_off.assign(T.n_heights + 1, 0);
-  T.fy_items.clear();
-  T.fr_items.clear();
-  T.br_items.clear();
-  T.fs_items.clear();
-  T.fr_shape.assign(T.n_heights, CoarseTileShape{4, 0});
-  T.br_shape.assign(T.n_heights, CoarseTileShape{4, 0});
-  for (int32_t h = 0; h < T.n_heights; ++h) {
-    // tile shapes from the longest row at this height: s for the forward
-    // rows of large nodes, b for the backward rows
-    int64_t lf = 0, lb = 0;
-    for (int32_t q = 0; q < nn; ++q) {
+  // --- tiles: per height one forward launch (leaves first) and one backward
+  // launch (roots first; nodes without boundary are done by the forward one)
+  T.tiles.clear();
+  T.fwd_launch.clear();
+  T.bwd_launch.clear();
+  std::vector<std::vector<int32_t>> at(maxh + 1);
+  for (int32_t q = 0; q < nn; ++q) at[T.fnodes[q].height].push_back(q);
+  auto add_launch = [&](int32_t h, bool forward) {
+    int64_t rows = 0, len = 0;
+    for (int32_t q : at[h]) {
       const FrontNode& F = T.fnodes[q];
-      if (F.height != h) continue;
-      if (!F.small) lf = std::max<int64_t>(lf, F.s);
-      lb = std::max<int64_t>(lb, F.b);
+      if (!forward && F.b == 0) continue;
+      rows += forward ? F.s + F.b : F.s;
+      len = std::max<int64_t>(len, forward ? F.s : F.b);
     }
-    T.fr_shape[h] = coarse_tile_shape(lf);
-    T.br_shape[h] = coarse_tile_shape(lb);
-    const int32_t tf = coarse_tile_rows(T.fr_shape[h]), tb = coarse_tile_rows(T.br_shape[h]);
-    for (int32_t q = 0; q < nn; ++q) {
+    if (rows == 0) return;
+    CoarseLaunch L{(int64_t)T.tiles.size(), 0, coarse_rows_per_wave(rows, len, forward), len > 128 ? 1 : 0};
+    for (int32_t q : at[h]) {
       const FrontNode& F = T.fnodes[q];
-      if (F.height != h) continue;
-      if (!F.small)  // small nodes assemble their y in the forward kernel
-        for (int32_t r = 0; r < F.s; ++r) T.fy_items.push_back((int32_t)(F.off + r));
-      if (F.small)
-        for (int32_t r = 0; r < (F.s + F.b + 63) / 64; ++r) T.fs_items.push_back(RowItem{q, r});
-      else
-        for (int32_t r = 0; r < F.s + F.b; r += tf) T.fr_items.push_back(RowItem{q, r});
-      for (int32_t r = 0; r < F.s; r += tb) T.br_items.push_back(RowItem{q, r});
+      if (!forward && F.b == 0) continue;
+      CoarseTile t{};
+      t.mat = forward ? F.fwd : F.bwd;
+      t.ld = forward ? F.lds : F.ldb;
+      t.len = forward ? F.s : F.b;
+      t.rows = forward ? F.s + F.b : F.s;
+      t.s = F.s;
+      t.off = (int32_t)F.off;
+      t.src = forward ? (int32_t)F.roff : (int32_t)F.bidx;
+      t.coff = (int32_t)F.coff;
+      t.root = F.b == 0;
+      for (t.row = 0; t.row < t.rows; t.row += 4 * L.rw) T.tiles.push_back(t);
     }
-    T.fy_off[h + 1] = (int32_t)T.fy_items.size();
-    T.fr_off[h + 1] = (int64_t)T.fr_items.size();
-    T.br_off[h + 1] = (int64_t)T.br_items.size();
-    T.fs_off[h + 1] = (int64_t)T.fs_items.size();
-  }
+    L.count = (int64_t)T.tiles.size() - L.first;
+    (forward ? T.fwd_launch : T.bwd_launch).push_back(L);
+  };
+  for (int32_t h = 0; h <= maxh; ++h) add_launch(h, true);
+  for (int32_t h = maxh; h >= 0; --h) add_launch(h, false);
   // largest sum of update matrices waiting for their parent (post-order stack)
   {
     int64_t cur = 0, mx = 0;
