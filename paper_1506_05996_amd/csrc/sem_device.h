@@ -87,6 +87,7 @@ struct sem_mesh_s {
   DBuf<CoarseTile> tiles;
   DBuf<int32_t> fb_idx, cvert, pslot, rs_off, part_dst, cdst, pre_slot, pre_row;
   bool in_capture = false;                // inside an enclosing capture: no graph of its own
+  bool one_stream = false;                // the preconditioner's coarse chain on the caller's stream
   int epb[2] = {0, 0};                    // operator tile (elements per workgroup) for FP64, FP32
   hipStream_t side_stream = nullptr;      // coarse chain of the preconditioner, beside the patch solves
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;

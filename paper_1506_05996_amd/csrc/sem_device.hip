@@ -611,7 +611,7 @@ void precond_dot(sem_mesh m, const T* r, T* z, int pc, int dot_dst, int dot_mode
     SEM_HIP(hipStreamWaitEvent(s, m->ev_join, 0));
   } else {
     hipStream_t sc = s;
-    if (coarse && fine) {
+    if (coarse && fine && !m->one_stream) {
       ensure_side_stream(m);
       SEM_HIP(hipEventRecord(m->ev_fork, s));
       SEM_HIP(hipStreamWaitEvent(m->side_stream, m->ev_fork, 0));
