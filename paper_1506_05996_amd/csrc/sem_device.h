@@ -91,10 +91,11 @@ struct sem_mesh_s {
   int epb[2] = {0, 0};                    // operator tile (elements per workgroup) for FP64, FP32
   hipStream_t side_stream = nullptr;      // coarse chain of the preconditioner, beside the patch solves
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  // PCG's convergence check read back without draining the stream: r . r and
-  // the breakdown flag land in pinned host memory, signalled by ev_check
+  // PCG's convergence check read back without draining the stream: the kernel
+  // that finishes r . r writes it and the breakdown flag to pinned host memory,
+  // two checks in turn, each signalled by its event
   double* check_host = nullptr;
-  hipEvent_t ev_check = nullptr;
+  hipEvent_t ev_check[2] = {nullptr, nullptr};
   hipStream_t capture_stream = nullptr;
   // lumped mass m_N for the mass term of the operator (uploaded when c != 0),
   // and the right-hand side of a heat-equation step
@@ -129,7 +130,7 @@ struct sem_mesh_s {
   // needs them) ...
   DBuf<double> v64[5];
   DBuf<float> v32[5];
-  DBuf<double> part, sc, dpart;
+  DBuf<double> part, sc, parts;
   // ... and the pointers one solve works in: the buffers above, or views into
   // the library's static scratch array (sem_pcg_solve_noalloc)
   struct SolveWork {
@@ -137,7 +138,8 @@ struct sem_mesh_s {
     float* v32[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     double* part = nullptr;   // kRedBlocks partial sums
     double* sc = nullptr;     // 16 device scalars of Algorithm 1
-    double* dpart = nullptr;  // per-workgroup partial dot products of the operator and preconditioner
+    // per-workgroup partial sums: p . A p, r . r, and r . z (patch solves, then coarse solve)
+    double *dpart = nullptr, *rpart = nullptr, *epart = nullptr;
   } wk;
   bool no_alloc = false;      // inside sem_pcg_solve_noalloc: no lazy set-up may run
 };

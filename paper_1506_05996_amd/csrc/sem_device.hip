@@ -251,20 +251,28 @@ int default_tile(int N) {
   return 1;
 }
 
+SharedNodes shared_nodes(sem_mesh m) {
+  const HostTables& T = m->T;
+  return SharedNodes{m->vinc_off.p, m->einc_off.p, m->fcount.p, m->dir.p,     T.V,
+                     T.base_f,      T.base_i,      T.N - 1,     T.wedge_off, T.wvert_off};
+}
+
+// the coefficients as the shared nodes need them (those per element are in the copies already)
+template <typename T>
+OpCoef<T> shared_coef(sem_mesh m) {
+  if (m->per_elem) return OpCoef<T>{T(1), T(0), nullptr, 0, nullptr, nullptr, nullptr, nullptr};
+  return op_coef<T>(m);
+}
+
 // the shared-node gather; as the operator's last step (u_op = the operator's
 // input) it also applies the coefficients, as the preconditioner's it only sums
 template <typename T>
-int64_t launch_gs(sem_mesh m, T* y, hipStream_t s, const T* pd = nullptr, double* dpart = nullptr,
-                  const T* u_op = nullptr) {
-  const HostTables& T_ = m->T;
-  const int64_t grid = blocks_for(T_.base_i);
+void launch_gs(sem_mesh m, T* y, hipStream_t s, const T* u_op = nullptr) {
   OpCoef<T> oc{T(1), T(0), nullptr, 0, nullptr, nullptr, nullptr, nullptr};
-  if (u_op != nullptr && !m->per_elem) oc = op_coef<T>(m);
-  hipLaunchKernelGGL((gs_kernel<T>), dim3((unsigned)grid), dim3(kGS), 0, s, y, Wp<T>(m), m->vinc_off.p,
-                     m->einc_off.p, m->fcount.p, m->dir.p, T_.V, T_.base_f, T_.base_i, T_.N - 1, T_.wedge_off,
-                     T_.wvert_off, pd, dpart, oc, u_op);
+  if (u_op != nullptr) oc = shared_coef<T>(m);
+  hipLaunchKernelGGL((gs_kernel<T>), dim3((unsigned)blocks_for(m->T.base_i)), dim3(kGS), 0, s, y, Wp<T>(m),
+                     shared_nodes(m), oc, u_op);
   SEM_HIP(hipGetLastError());
-  return grid;
 }
 
 // element kernel only (the gather follows separately); returns the grid size
@@ -285,82 +293,72 @@ int64_t apply_A_elements(sem_mesh m, const T* u, T* y, hipStream_t s, double* dp
 template <typename T>
 void apply_A(sem_mesh m, const T* u, T* y, hipStream_t s) {
   apply_A_elements<T>(m, u, y, s);
-  launch_gs<T>(m, y, s, nullptr, nullptr, u);
+  launch_gs<T>(m, y, s, u);
 }
 
-// the n partial sums in the work's dpart into scalar slot dst (dot_final mode
-// `mode`): through kRedBlocks chunk sums when there are many; a single launch
-// when there are at most kRedBlocks (the chunk sums would then copy them one
-// by one, so the result is the same bit for bit)
-void reduce_partials(sem_mesh m, int64_t n, int dst, int mode, hipStream_t s) {
-  if (n <= kRedBlocks) {
-    hipLaunchKernelGGL(dot_final_kernel, dim3(1), dim3(kRedThreads), 0, s, (const double*)m->wk.dpart, m->wk.sc, (int)n,
-                       dst, mode);
-  } else {
+// n partial sums into the scalars (see pcg_scalar): one launch up to kOneSum,
+// through kRedBlocks chunk sums beyond
+void reduce_partials(sem_mesh m, const double* part, int64_t n, int dst, int mode, hipStream_t s, int rz_in = 0,
+                     int rz_out = 0, double* host = nullptr) {
+  if (n > kOneSum) {
     const int64_t chunk = (n + kRedBlocks - 1) / kRedBlocks;
     const int nb = (int)((n + chunk - 1) / chunk);
-    hipLaunchKernelGGL(sum_chunks_kernel, dim3(nb), dim3(kRedThreads), 0, s, (const double*)m->wk.dpart, m->wk.part,
-                       n, chunk);
-    hipLaunchKernelGGL(dot_final_kernel, dim3(1), dim3(kRedThreads), 0, s, m->wk.part, m->wk.sc, nb, dst, mode);
+    hipLaunchKernelGGL(sum_chunks_kernel, dim3(nb), dim3(kRedThreads), 0, s, part, m->wk.part, n, chunk);
+    part = m->wk.part;
+    n = nb;
   }
+  hipLaunchKernelGGL(dot_final_kernel, dim3(1), dim3(kFinalThreads), 0, s, part, m->wk.sc, (int)n, dst, mode, rz_in,
+                     rz_out, host);
   SEM_HIP(hipGetLastError());
 }
 
-// y = A u and u . y into the scalar slot dst (dot_final mode `mode`), the dot
-// product taken from the operator's own kernels (no extra pass over u and y)
-template <typename T>
-void apply_A_dot(sem_mesh m, const T* u, T* y, int dst, int mode, hipStream_t s) {
-  const int64_t na = apply_A_elements<T>(m, u, y, s, m->wk.dpart);
-  const int64_t ng = launch_gs<T>(m, y, s, u, m->wk.dpart + na, u);
-  const int64_t n = na + ng;
-  reduce_partials(m, n, dst, mode, s);
-}
+// Up to so many partial sums the kernel that needs the scalar sums them itself,
+// in every workgroup, instead of a launch of its own in between (about 5 us):
+// a handful of loads per lane, and few enough workgroups.
+constexpr int64_t kConsumerSum = 512;
 
 // --- fine and coarse preconditioner -----------------------------------------
+template <int N>
+int64_t fdm_grid(sem_mesh m) { return xcd_grid((m->T.E + fdm_ppb<N>() - 1) / fdm_ppb<N>()); }
+
 template <int N, typename T>
-void launch_fdm(sem_mesh m, const T* r, hipStream_t s) {
+void launch_fdm(sem_mesh m, const T* r, hipStream_t s, double* epart) {
   T* zc = ZOp<T>(m);
   T* zx = zc + m->T.E * (int64_t)m->T.n1 * m->T.n1 * m->T.n1;
-  hipLaunchKernelGGL((fdm_kernel<N, T>), dim3((unsigned)xcd_grid((m->T.E + fdm_ppb<N>() - 1) / fdm_ppb<N>())), dim3(fdm_threads<N>()), 0, s, r, zc, zx,
+  hipLaunchKernelGGL((fdm_kernel<N, T>), dim3((unsigned)fdm_grid<N>(m)), dim3(fdm_threads<N>()), 0, s, r, zc, zx,
                      m->ip.p, m->xdest.p, Sp<T>(m), Lp<T>(m), Hp<T>(m), m->order.p, m->T.E,
                      (T)m->T.kappa, (T)m->T.cmass, m->per_elem ? KEp<T>(m) : nullptr,
-                     m->per_elem ? CEp<T>(m) : nullptr);
+                     m->per_elem ? CEp<T>(m) : nullptr, epart);
   SEM_HIP(hipGetLastError());
 }
 
-// element-wise sum of the corrections (+ coarse interpolation) into z and w
-template <int N, typename T>
-int64_t launch_schwarz_sum(sem_mesh m, T* z, bool fine, const double* Zv, hipStream_t s, const T* rd,
-                           double* dpart) {
+// element-wise sum of the corrections (+ coarse interpolation), interiors as
+// MODE says (z: the result, or p), shared nodes to the work array
+template <int N, typename T, int MODE>
+void launch_schwarz_sum(sem_mesh m, T* z, T* x, bool fine, const double* Zv, hipStream_t s, int rz_in, int rz_out,
+                        const double* bpart, int nb) {
   constexpr int EPB = ax_epb<N>();
   const T* zc = ZOp<T>(m);
   const T* zx = zc + m->T.E * (int64_t)m->T.n1 * m->T.n1 * m->T.n1;
-  const int64_t grid = xcd_grid((m->T.E + EPB - 1) / EPB);
-  hipLaunchKernelGGL((schwarz_sum_kernel<N, T, EPB>), dim3((unsigned)grid), dim3(EPB * (N + 1) * (N + 1)), 0, s, z,
-                     Wp<T>(m), zc, zx, m->rec.p, m->dir.p, m->order.p, m->T.E, (int)fine, Zv, m->phi.p, rd, dpart);
+  hipLaunchKernelGGL((schwarz_sum_kernel<N, T, EPB, MODE>), dim3((unsigned)xcd_grid((m->T.E + EPB - 1) / EPB)),
+                     dim3(EPB * (N + 1) * (N + 1)), 0, s, z, x, Wp<T>(m), zc, zx, m->rec.p, m->dir.p, m->order.p,
+                     m->T.E, (int)fine, Zv, m->phi.p, m->wk.sc, rz_in, rz_out, bpart, nb);
   SEM_HIP(hipGetLastError());
-  return grid;
 }
 
-// the preconditioner's result from the patch corrections and the coarse
-// interpolation; with dpart, also the partial sums of rd . z (returns their count)
-template <typename T>
-int64_t schwarz_sum(sem_mesh m, T* z, bool fine, const double* Zv, hipStream_t s, const T* rd = nullptr,
-                    double* dpart = nullptr) {
-  int64_t na = 0;
+template <typename T, int MODE>
+void schwarz_sum(sem_mesh m, T* z, T* x, bool fine, const double* Zv, hipStream_t s, int rz_in = 0, int rz_out = 0,
+                 const double* bpart = nullptr, int nb = 0) {
   switch (m->T.N) {
-#define CASE(NN)                                                     \
-  case NN:                                                           \
-    na = launch_schwarz_sum<NN, T>(m, z, fine, Zv, s, rd, dpart);    \
-    break;
+#define CASE(NN) \
+  case NN:       \
+    return launch_schwarz_sum<NN, T, MODE>(m, z, x, fine, Zv, s, rz_in, rz_out, bpart, nb);
     CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14)
     CASE(15)
 #undef CASE
     default:
       throw Error{SEM_EUNSUPPORTED, "order not compiled"};
   }
-  const int64_t ng = launch_gs<T>(m, z, s, rd, dpart != nullptr ? dpart + na : nullptr);
-  return na + ng;
 }
 
 template <int N, typename T>
@@ -371,13 +369,40 @@ void launch_restrict(sem_mesh m, const T* r, hipStream_t s) {
 }
 
 template <typename T>
-void fdm_and_restrict(sem_mesh m, const T* r, bool fine, bool coarse, hipStream_t s) {
+void launch_restrict(sem_mesh m, const T* r, hipStream_t s) {
   switch (m->T.N) {
-#define CASE(NN)                                        \
-  case NN:                                              \
-    if (fine) launch_fdm<NN, T>(m, r, s);               \
-    if (coarse) launch_restrict<NN, T>(m, r, s);        \
-    break;
+#define CASE(NN) \
+  case NN:       \
+    return launch_restrict<NN, T>(m, r, s);
+    CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14)
+    CASE(15)
+#undef CASE
+    default:
+      throw Error{SEM_EUNSUPPORTED, "order not compiled"};
+  }
+}
+
+// the patch solves; with epart, also the partial sums of their share of r . z
+template <typename T>
+void launch_fdm(sem_mesh m, const T* r, hipStream_t s, double* epart = nullptr) {
+  switch (m->T.N) {
+#define CASE(NN) \
+  case NN:       \
+    return launch_fdm<NN, T>(m, r, s, epart);
+    CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14)
+    CASE(15)
+#undef CASE
+    default:
+      throw Error{SEM_EUNSUPPORTED, "order not compiled"};
+  }
+}
+
+// workgroups of the patch solves (their partial sums)
+int64_t fdm_blocks(sem_mesh m) {
+  switch (m->T.N) {
+#define CASE(NN) \
+  case NN:       \
+    return fdm_grid<NN>(m);
     CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14)
     CASE(15)
 #undef CASE
@@ -388,14 +413,15 @@ void fdm_and_restrict(sem_mesh m, const T* r, bool fine, bool coarse, hipStream_
 
 // one launch of the forward or backward sweep
 template <int RW, bool NARROW>
-void launch_coarse_tiles(sem_mesh m, hipStream_t s, const CoarseLaunch& L, bool forward) {
+void launch_coarse_tiles(sem_mesh m, hipStream_t s, const CoarseLaunch& L, bool forward, double* epart) {
   const CoarseTile* tiles = m->tiles.p + L.first;
   if (forward) {
     const int n_pre = L.first == 0 ? (int)m->T.pre_row.size() : 0;  // the lowest launch sums the higher rows' parts
     hipLaunchKernelGGL((coarse_fwd_kernel<RW, NARROW>), dim3((unsigned)(L.count + (n_pre + 255) / 256)), dim3(256), 0,
                        s, m->Xlev.p, m->Zv.p, m->cvec.p, (const double*)m->fwd_pool.p, tiles,
                        (const int32_t*)m->rs_off.p, (const int32_t*)m->cdst.p, (const int32_t*)m->cvert.p,
-                       (int)L.count, (const int32_t*)m->pre_slot.p, (const int32_t*)m->pre_row.p, n_pre);
+                       (int)L.count, (const int32_t*)m->pre_slot.p, (const int32_t*)m->pre_row.p, n_pre,
+                       epart != nullptr ? epart + L.first : nullptr);
   } else {
     hipLaunchKernelGGL((coarse_bwd_kernel<RW, NARROW>), dim3((unsigned)L.count), dim3(256), 0, s, m->Xlev.p, m->Zv.p,
                        (const double*)m->bwd_pool.p, tiles, (const int32_t*)m->fb_idx.p, (const int32_t*)m->cvert.p);
@@ -403,26 +429,27 @@ void launch_coarse_tiles(sem_mesh m, hipStream_t s, const CoarseLaunch& L, bool 
   SEM_HIP(hipGetLastError());
 }
 
-void launch_coarse(sem_mesh m, hipStream_t s, const CoarseLaunch& L, bool forward) {
+void launch_coarse(sem_mesh m, hipStream_t s, const CoarseLaunch& L, bool forward, double* epart = nullptr) {
   if (!L.wide) {
     switch (L.rw) {
-      case 1: return launch_coarse_tiles<1, true>(m, s, L, forward);
-      case 2: return launch_coarse_tiles<2, true>(m, s, L, forward);
-      case 4: return launch_coarse_tiles<4, true>(m, s, L, forward);
-      default: return launch_coarse_tiles<8, true>(m, s, L, forward);
+      case 1: return launch_coarse_tiles<1, true>(m, s, L, forward, epart);
+      case 2: return launch_coarse_tiles<2, true>(m, s, L, forward, epart);
+      case 4: return launch_coarse_tiles<4, true>(m, s, L, forward, epart);
+      default: return launch_coarse_tiles<8, true>(m, s, L, forward, epart);
     }
   }
   switch (L.rw) {
-    case 1: return launch_coarse_tiles<1, false>(m, s, L, forward);
-    case 2: return launch_coarse_tiles<2, false>(m, s, L, forward);
-    default: return launch_coarse_tiles<4, false>(m, s, L, forward);
+    case 1: return launch_coarse_tiles<1, false>(m, s, L, forward, epart);
+    case 2: return launch_coarse_tiles<2, false>(m, s, L, forward, epart);
+    default: return launch_coarse_tiles<4, false>(m, s, L, forward, epart);
   }
 }
 
 // element parts in the contribution vector -> Zv (vertex order; 0 on Dirichlet
-// vertices since set-up): nested-dissection sweeps
-void coarse_sweeps(sem_mesh m, hipStream_t s) {
-  for (const CoarseLaunch& L : m->T.fwd_launch) launch_coarse(m, s, L, true);
+// vertices since set-up): nested-dissection sweeps; with epart, the partial
+// sums of R . Z (one per forward tile)
+void coarse_sweeps(sem_mesh m, hipStream_t s, double* epart = nullptr) {
+  for (const CoarseLaunch& L : m->T.fwd_launch) launch_coarse(m, s, L, true, epart);
   for (const CoarseLaunch& L : m->T.bwd_launch) launch_coarse(m, s, L, false);
 }
 
@@ -514,22 +541,19 @@ void amg_fcg2(sem_mesh m, int l, const double* b, double* x, hipStream_t s) {
   SEM_HIP(hipGetLastError());
 }
 
-// element parts in the contribution vector -> Zv (vertex order) by one K-cycle
-void amg_sweeps(sem_mesh m, hipStream_t s) {
-  const HostTables& T = m->T;
+// one K-cycle from the element parts in the contribution vector to level 0's solution
+void amg_cycle(sem_mesh m, hipStream_t s) {
   auto& d0 = *m->amg[0];
   hipLaunchKernelGGL(amg_in_kernel, dim3((unsigned)blocks_for(d0.n)), dim3(kGS), 0, s, d0.B.p, m->cvec.p, m->rs_off.p,
                      m->pslot.p, m->cvert.p, m->vinc_off.p, m->amg_nd.p, d0.n);
   amg_kcycle(m, 0, d0.B.p, d0.X.p, s);
-  hipLaunchKernelGGL(amg_out_kernel, dim3((unsigned)blocks_for(T.V)), dim3(kGS), 0, s, m->Zv.p, d0.X.p, m->cidx.p,
-                     m->amg_pos.p, T.V);
-  SEM_HIP(hipGetLastError());
 }
 
 // Capture one K-cycle (some 200 small launches) once, on a private stream; the
-// preconditioner replays it on the caller's stream.  Built at set-up and
-// whenever the coarse matrix or solver changes.  The exact solve needs none:
-// it is a handful of launches.
+// preconditioner replays it on the caller's stream, then forms the vertex values
+// (and R . Z) with one more launch.  Built at set-up and whenever the coarse
+// matrix or solver changes.  The exact solve needs none: it is a handful of
+// launches.
 void build_coarse_graph(sem_mesh m) {
   if (m->T.nc == 0 || m->coarse_solver != SEM_COARSE_AMG) return;
   if (m->amg.empty()) throw Error{SEM_EINVAL, "AMG hierarchy not built"};
@@ -539,7 +563,7 @@ void build_coarse_graph(sem_mesh m) {
   hipGraph_t g = nullptr;
   SEM_HIP(hipStreamBeginCapture(m->capture_stream, hipStreamCaptureModeThreadLocal));
   try {
-    amg_sweeps(m, m->capture_stream);
+    amg_cycle(m, m->capture_stream);
   } catch (...) {
     (void)hipStreamEndCapture(m->capture_stream, &g);
     if (g) (void)hipGraphDestroy(g);
@@ -554,12 +578,29 @@ void build_coarse_graph(sem_mesh m) {
   }
 }
 
-// element parts in the contribution vector -> Zv (vertex order): the coarse solve P_0
-void coarse_solve_tree(sem_mesh m, hipStream_t s) {
-  if (m->coarse_solver != SEM_COARSE_AMG) return coarse_sweeps(m, s);
-  if (m->in_capture) return amg_sweeps(m, s);  // inside an enclosing capture: the kernels themselves
-  build_coarse_graph(m);
-  SEM_HIP(hipGraphLaunch(m->amg_graph, s));
+// element parts in the contribution vector -> Zv (vertex order): the coarse
+// solve P_0; with epart, also the partial sums of R . Z
+void coarse_solve_tree(sem_mesh m, hipStream_t s, double* epart = nullptr) {
+  if (m->coarse_solver != SEM_COARSE_AMG) return coarse_sweeps(m, s, epart);
+  if (m->in_capture) {  // inside an enclosing capture: the kernels themselves
+    amg_cycle(m, s);
+  } else {
+    build_coarse_graph(m);
+    SEM_HIP(hipGraphLaunch(m->amg_graph, s));
+  }
+  auto& d0 = *m->amg[0];
+  hipLaunchKernelGGL(amg_out_kernel, dim3((unsigned)blocks_for(m->T.V)), dim3(kGS), 0, s, m->Zv.p, d0.X.p, d0.B.p,
+                     m->cidx.p, m->amg_pos.p, m->T.V, epart);
+  SEM_HIP(hipGetLastError());
+}
+
+// number of the partial sums of R . Z
+int64_t coarse_parts(sem_mesh m) {
+  if (m->T.nc == 0) return 0;
+  if (m->coarse_solver == SEM_COARSE_AMG) return blocks_for(m->T.V);
+  int64_t n = 0;
+  for (const CoarseLaunch& L : m->T.fwd_launch) n += L.count;
+  return n;
 }
 
 // the second stream (and its fork/join events) that runs the coarse chain
@@ -572,101 +613,113 @@ void ensure_side_stream(sem_mesh m) {
   SEM_HIP(hipEventCreateWithFlags(&m->ev_join, hipEventDisableTiming));
 }
 
-template <typename T>
-void precond_dot(sem_mesh m, const T* r, T* z, int pc, int dot_dst, int dot_mode, hipStream_t s,
-                 bool coarse_started = false);
+// Whether the coarse solve runs on the second stream, beside the patch solves.
+// The exact solve's few launches run before them on the caller's stream: the
+// patch solves fill every CU, so that each height waited for their workgroups
+// to end, and the hand-overs between the streams cost about 10 us each (beside /
+// before: 24^3, N = 7 PCG 18.0 / 17.5 ms, 56^3 212.8 / 208.8 ms, 40^3 refined 59.0 /
+// 59.7 ms; preconditioner alone 16^3 79 / 72 us, 40^3 826 / 809 us).  A K-cycle of
+// some 200 small launches is worth hiding.
+bool coarse_beside(sem_mesh m) { return !m->one_stream && m->coarse_solver == SEM_COARSE_AMG; }
 
-template <typename T>
-void precond(sem_mesh m, const T* r, T* z, int pc, hipStream_t s) {
-  precond_dot<T>(m, r, z, pc, -1, 0, s);
+// what follows on s runs beside the coarse chain on the returned stream
+hipStream_t fork_coarse(sem_mesh m, hipStream_t s) {
+  if (!coarse_beside(m)) return s;
+  ensure_side_stream(m);
+  SEM_HIP(hipEventRecord(m->ev_fork, s));
+  SEM_HIP(hipStreamWaitEvent(m->side_stream, m->ev_fork, 0));
+  return m->side_stream;
 }
 
-template <typename TA, typename TB>
-void dot(sem_mesh m, const TA* a, const TB* b, int dst, int mode, hipStream_t s);
-
-// z = P r; with dot_dst >= 0 also r . z into scalar slot dot_dst (dot_final
-// mode dot_mode), taken from the preconditioner's own output kernels
-// coarse_started: the coarse chain of this application (restriction, coarse
-// solve) is already running on the side stream (pcg_core forks it right after
-// the update of r); only its join remains.
+// z = P r (assembled); the coarse and fine parts are independent until the final sum
 template <typename T>
-void precond_dot(sem_mesh m, const T* r, T* z, int pc, int dot_dst, int dot_mode, hipStream_t s,
-                 bool coarse_started) {
+void precond(sem_mesh m, const T* r, T* z, int pc, hipStream_t s) {
   const HostTables& H = m->T;
   const bool fine = pc & SEM_PC_FINE, coarse = (pc & SEM_PC_COARSE) && H.nc > 0;
   if (pc == SEM_PC_NONE) {
     hipLaunchKernelGGL((copy_kernel<T, T>), dim3(grid_stride_blocks(H.n_global)), dim3(kGS), 0, s, z, r, H.n_global);
     SEM_HIP(hipGetLastError());
-    if (dot_dst >= 0) dot<T, T>(m, r, z, dot_dst, dot_mode, s);
     return;
   }
-  // The coarse and fine parts are independent until the final sum: the
-  // coarse chain (restriction, coarse sweeps) runs on a second stream while
-  // the patch solves run on the caller's stream; both join before the sum.
-  // The coarse chain is issued first: it is the longer dependent chain on all
-  // but the largest meshes, and its workgroups otherwise queue behind the patch
-  // solves', which fill every CU.
-  if (coarse_started) {
-    fdm_and_restrict<T>(m, r, true, false, s);
-    SEM_HIP(hipStreamWaitEvent(s, m->ev_join, 0));
-  } else {
-    hipStream_t sc = s;
-    if (coarse && fine && !m->one_stream) {
-      ensure_side_stream(m);
-      SEM_HIP(hipEventRecord(m->ev_fork, s));
-      SEM_HIP(hipStreamWaitEvent(m->side_stream, m->ev_fork, 0));
-      sc = m->side_stream;
-    }
-    if (coarse) {
-      fdm_and_restrict<T>(m, r, false, true, sc);
-      coarse_solve_tree(m, sc);
-      if (sc != s) SEM_HIP(hipEventRecord(m->ev_join, sc));
-    }
-    if (fine) fdm_and_restrict<T>(m, r, true, false, s);
-    if (sc != s) SEM_HIP(hipStreamWaitEvent(s, m->ev_join, 0));
+  hipStream_t sc = s;
+  if (coarse) {
+    if (fine) sc = fork_coarse(m, s);
+    launch_restrict<T>(m, r, sc);
+    coarse_solve_tree(m, sc);
+    if (sc != s) SEM_HIP(hipEventRecord(m->ev_join, sc));
   }
-  if (dot_dst < 0) {
-    schwarz_sum<T>(m, z, fine, coarse ? (const double*)m->Zv.p : nullptr, s);
-    return;
-  }
-  const int64_t n = schwarz_sum<T>(m, z, fine, coarse ? (const double*)m->Zv.p : nullptr, s, r, m->wk.dpart);
-  reduce_partials(m, n, dot_dst, dot_mode, s);
+  if (fine) launch_fdm<T>(m, r, s);
+  if (sc != s) SEM_HIP(hipStreamWaitEvent(s, m->ev_join, 0));
+  schwarz_sum<T, kSumZ>(m, z, nullptr, fine, coarse ? (const double*)m->Zv.p : nullptr, s);
+  launch_gs<T>(m, z, s);
 }
 
-// PCG's update of r fused with the coarse restriction (update_r_restrict_kernel),
-// r . r into scalar slot 4, then the rest of the coarse chain (the coarse
-// solve) forked onto the side stream; precond_dot(..., true) joins it.
+// --- the steps of a PCG iteration -----------------------------------------------
+// r -= alpha A p at the interiors, with r . r and (cvec) the element parts of the
+// coarse residual over all nodes; returns the number of partial sums of r . r
 template <int N, typename T>
-int64_t launch_update_r_restrict(sem_mesh m, T* r, const T* w, hipStream_t s) {
-  const int64_t grid = xcd_grid(m->T.E);
-  hipLaunchKernelGGL((update_r_restrict_kernel<N, T>), dim3((unsigned)grid), dim3((N + 1) * (N + 1)), 0, s, r, w,
-                     (const double*)m->wk.sc, m->cvec.p, m->part_dst.p, m->wk.dpart, m->rec.p,
+int64_t launch_update_r(sem_mesh m, T* r, const T* y, bool coarse, hipStream_t s) {
+  constexpr int EPB = ax_epb<N>();
+  const int64_t grid = xcd_grid((m->T.E + EPB - 1) / EPB);
+  hipLaunchKernelGGL((update_r_kernel<N, T, EPB>), dim3((unsigned)grid), dim3(EPB * (N + 1) * (N + 1)), 0, s, r, y,
+                     (const double*)m->wk.sc, coarse ? m->cvec.p : nullptr, m->part_dst.p, m->wk.rpart, m->rec.p,
                      (const double*)m->phi.p, m->order.p, m->T.E);
   SEM_HIP(hipGetLastError());
   return grid;
 }
 
+// alpha = rz / (p . A p) and r -= alpha A p; returns the number of partial sums of r . r
 template <typename T>
-void update_r_and_fork_coarse(sem_mesh m, T* r, const T* w, hipStream_t s) {
-  int64_t n = 0;
+int64_t pcg_update_r(sem_mesh m, T* r, const T* p, T* y, int rz, bool coarse, hipStream_t s) {
+  int64_t na = apply_A_elements<T>(m, p, y, s, m->wk.dpart);
+  if (na > kConsumerSum) {
+    reduce_partials(m, m->wk.dpart, na, 1, 1, s, rz);
+    na = 0;
+  }
+  hipLaunchKernelGGL((gs_r_kernel<T>), dim3((unsigned)blocks_for(m->T.base_i)), dim3(kGS), 0, s, r, Wp<T>(m),
+                     shared_nodes(m), shared_coef<T>(m), p, m->wk.sc, rz, (const double*)m->wk.dpart, (int)na);
+  SEM_HIP(hipGetLastError());
   switch (m->T.N) {
-#define CASE(NN)                                             \
-  case NN:                                                   \
-    n = launch_update_r_restrict<NN, T>(m, r, w, s);         \
-    break;
+#define CASE(NN) \
+  case NN:       \
+    return launch_update_r<NN, T>(m, r, y, coarse, s);
     CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14)
     CASE(15)
 #undef CASE
     default:
       throw Error{SEM_EUNSUPPORTED, "order not compiled"};
   }
-  reduce_partials(m, n, 4, 0, s);
-  ensure_side_stream(m);
-  hipStream_t sc = m->side_stream;
-  SEM_HIP(hipEventRecord(m->ev_fork, s));
-  SEM_HIP(hipStreamWaitEvent(sc, m->ev_fork, 0));
-  coarse_solve_tree(m, sc);
-  SEM_HIP(hipEventRecord(m->ev_join, sc));
+}
+
+// the coarse solve of the element parts in the contribution vector, its partial
+// sums of r . z after those of the patch solves
+void pcg_start_coarse(sem_mesh m, bool fine, hipStream_t s) {
+  hipStream_t sc = fine ? fork_coarse(m, s) : s;
+  coarse_solve_tree(m, sc, m->wk.epart + (fine ? fdm_blocks(m) : 0));
+  if (sc != s) SEM_HIP(hipEventRecord(m->ev_join, sc));
+}
+
+// the rest of an iteration: the patch solves, beta = (r . z) / rz, and x += alpha p,
+// p = z + beta p (start: p = z and rz alone)
+template <typename T>
+void pcg_finish(sem_mesh m, const T* r, T* x, T* p, bool fine, bool coarse, int rz_in, int rz_out, bool start,
+                hipStream_t s) {
+  if (fine) launch_fdm<T>(m, r, s, m->wk.epart);
+  if (fine && coarse && coarse_beside(m)) SEM_HIP(hipStreamWaitEvent(s, m->ev_join, 0));
+  const double* Zv = coarse ? (const double*)m->Zv.p : nullptr;
+  const int64_t n = (fine ? fdm_blocks(m) : 0) + (coarse ? coarse_parts(m) : 0);
+  if (start) {
+    reduce_partials(m, m->wk.epart, n, rz_out, 0, s);
+    schwarz_sum<T, kSumStart>(m, p, nullptr, fine, Zv, s);
+  } else if (n > 0 && n <= kConsumerSum) {
+    schwarz_sum<T, kSumPx>(m, p, x, fine, Zv, s, rz_in, rz_out, (const double*)m->wk.epart, (int)n);
+  } else {
+    reduce_partials(m, m->wk.epart, n, 5, 2, s, rz_in, rz_out);
+    schwarz_sum<T, kSumPx>(m, p, x, fine, Zv, s);
+  }
+  hipLaunchKernelGGL((gs_px_kernel<T>), dim3((unsigned)blocks_for(m->T.base_i)), dim3(kGS), 0, s, x, p, Wp<T>(m),
+                     shared_nodes(m), (const double*)m->wk.sc, (int)start);
+  SEM_HIP(hipGetLastError());
 }
 
 // --- coarse factorisation (set-up), multifrontal in post-order.  Node t's
@@ -897,32 +950,44 @@ void upload_all(sem_mesh m) {
   m->part.alloc(kRedBlocks);
   m->sc.alloc(16);
   ensure_side_stream(m);
+  SEM_HIP(hipHostMalloc((void**)&m->check_host, 4 * sizeof(double), hipHostMallocDefault));
+  for (auto& e : m->ev_check) SEM_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   factor_coarse(m);
 }
 
-// partial dot products of the operator and the preconditioner's sum (one per
-// element workgroup at most, one per gather workgroup)
-size_t dpart_count(sem_mesh m) { return (size_t)(xcd_grid(m->T.E) + blocks_for(m->T.base_i)); }
+// partial sums of one solve: p . A p and r . r (one per element workgroup at
+// most), r . z (one per workgroup of the patch solves and of the coarse solve)
+struct PartCounts {
+  size_t d, r, e;
+  size_t total() const { return d + r + e; }
+};
+PartCounts part_counts(sem_mesh m) {
+  const size_t n = (size_t)xcd_grid(m->T.E);
+  return PartCounts{n, n, (size_t)(fdm_blocks(m) + coarse_parts(m))};
+}
 
-// the handle's own solve buffers (allocated on first need) as the work of the next solve
+void set_parts(sem_mesh m, double* base) {
+  const PartCounts c = part_counts(m);
+  m->wk.dpart = base;
+  m->wk.rpart = base + c.d;
+  m->wk.epart = base + c.d + c.r;
+}
+
+// the handle's own solve buffers (allocated on first need) as the work of the
+// next solve (vector 2 of each set is not used)
 void ensure_work(sem_mesh m, bool need32) {
   const int64_t n = m->T.n_global;
-  for (auto& b : m->v64)
-    if (b.n != (size_t)n) b.alloc(n);
-  const size_t nd = dpart_count(m);
-  if (m->dpart.n < nd) m->dpart.alloc(nd);
-  if (need32)
-    for (auto& b : m->v32)
-      if (b.n != (size_t)n) b.alloc(n);
+  const size_t np = part_counts(m).total();
+  if (m->parts.n < np) m->parts.alloc(np);
   for (int q = 0; q < 5; ++q) {
+    if (q != 2 && m->v64[q].n != (size_t)n) m->v64[q].alloc(n);
+    if (q != 2 && need32 && m->v32[q].n != (size_t)n) m->v32[q].alloc(n);
     m->wk.v64[q] = m->v64[q].p;
     m->wk.v32[q] = need32 ? m->v32[q].p : nullptr;
   }
   m->wk.part = m->part.p;
   m->wk.sc = m->sc.p;
-  m->wk.dpart = m->dpart.p;
-  if (!m->check_host) SEM_HIP(hipHostMalloc((void**)&m->check_host, 4 * sizeof(double), hipHostMallocDefault));
-  if (!m->ev_check) SEM_HIP(hipEventCreateWithFlags(&m->ev_check, hipEventDisableTiming));
+  set_parts(m, m->parts.p);
 }
 
 // --- static scratch of sem_pcg_solve_noalloc ------------------------------
@@ -955,7 +1020,7 @@ double* scratch_of(int device) {
 
 // byte offsets of one solve's work inside the scratch array (256-aligned parts)
 struct ScratchLayout {
-  size_t sc, part, dpart, v64, v32, total;
+  size_t sc, part, v64, v32, total;
 };
 
 ScratchLayout scratch_layout(sem_mesh m, bool need32) {
@@ -967,8 +1032,7 @@ ScratchLayout scratch_layout(sem_mesh m, bool need32) {
   o += up(16 * sizeof(double));
   L.part = o;
   o += up(kRedBlocks * sizeof(double));
-  L.dpart = o;
-  o += up(dpart_count(m) * sizeof(double));
+  o += up((size_t)(xcd_grid(m->T.E) + blocks_for(m->T.base_i)) * sizeof(double));  // not used
   L.v64 = o;
   o += 5 * up(n * sizeof(double));
   L.v32 = o;
@@ -989,18 +1053,20 @@ void scratch_work(sem_mesh m, bool need32, double* base) {
   }
   m->wk.part = reinterpret_cast<double*>(c + L.part);
   m->wk.sc = reinterpret_cast<double*>(c + L.sc);
-  m->wk.dpart = reinterpret_cast<double*>(c + L.dpart);
+  // vector 2 is not used by the solve: its place takes the partial sums (at most
+  // about three per element, against at least eight nodes)
+  if (part_counts(m).total() > n) throw Error{SEM_EINVAL, "static scratch: partial sums do not fit"};
+  set_parts(m, m->wk.v64[2]);
 }
 
 template <typename TA, typename TB>
-void dot(sem_mesh m, const TA* a, const TB* b, int dst, int mode, hipStream_t s) {
+void dot(sem_mesh m, const TA* a, const TB* b, int dst, hipStream_t s) {
   const int64_t n = m->T.n_global;
   const int nb = (int)std::min<int64_t>(kRedBlocks, blocks_for(n, kRedThreads));
   hipLaunchKernelGGL((dot_partial_kernel<TA, TB>), dim3(nb), dim3(kRedThreads), 0, s, a, b, m->wk.part, n,
                      (int)aligned16(a, b));
   SEM_HIP(hipGetLastError());
-  hipLaunchKernelGGL(dot_final_kernel, dim3(1), dim3(kRedThreads), 0, s, m->wk.part, m->wk.sc, nb, dst, mode);
-  SEM_HIP(hipGetLastError());
+  reduce_partials(m, m->wk.part, nb, dst, 0, s);
 }
 
 double read_scalar(sem_mesh m, int idx, hipStream_t s) {
@@ -1015,96 +1081,117 @@ double read_scalar(sem_mesh m, int idx, hipStream_t s) {
 // iterations, *rel the last ||r|| / ||b||.  A start that already meets the
 // tolerance returns at once; after a breakdown x keeps the last finite iterate
 // (the vector updates skip themselves once the flag is set).
+//
+// One iteration is nine launches and the coarse solve's (two sums fewer on
+// small meshes): the operator's element kernel with p . A p; alpha; r -= alpha A p
+// at the shared nodes, with the gather of A p, then at the interiors, with r . r
+// and the coarse restriction; r . r to the host; the coarse solve; the patch
+// solves with r . z; beta; the sum of the corrections into x and p at the
+// interiors, then at the shared nodes.  The
+// scalar products need no assembled vector, so neither A p at the shared nodes
+// nor z is ever stored.  Against the gathers and vector updates as passes of
+// their own: PCG to 1e-10 at 24^3, N = 7 19.2 -> 17.5 ms, 56^3 218 -> 209 ms, 4^3,
+// N = 4 3.0 -> 1.8 ms, 40^3 refined 62.8 -> 59.7 ms.
 template <typename T>
 int pcg_core(sem_mesh m, T* x, T* r, double bnorm2, double rr0, double rtol, int max_iter, int pc, int check_every,
              hipStream_t s, int* iters, double* rel, sem_solve_stats* st) {
-  T* z;
   T* p;
   T* w;
   if constexpr (std::is_same<T, double>::value) {
-    z = m->wk.v64[2];
     p = m->wk.v64[3];
     w = m->wk.v64[4];
   } else {
-    z = m->wk.v32[2];
     p = m->wk.v32[3];
     w = m->wk.v32[4];
   }
   double* sc = m->wk.sc;
   const int64_t n = m->T.n_global;
-  const int nb = (int)std::min<int64_t>(kRedBlocks, blocks_for(n, kRedThreads));
   const int gb = grid_stride_blocks(n);
   const double tol2 = rtol * rtol * bnorm2;
+  const bool fine = pc & SEM_PC_FINE, coarse = (pc & SEM_PC_COARSE) && m->T.nc > 0;
   int k = 0;
   double rr = rr0;
   *iters = 0;
   *rel = std::sqrt(rr / bnorm2);
   if (rr <= tol2) return SEM_OK;
   hipLaunchKernelGGL((fill_kernel<double>), dim3(1), dim3(kGS), 0, s, sc, 0.0, (int64_t)7);
-  precond_dot<T>(m, r, z, pc, 0, 0, s);
-  hipLaunchKernelGGL((copy_kernel<T, T>), dim3(gb), dim3(kGS), 0, s, p, z, n);
-  int status = SEM_ENOCONV;
-  bool pending_x = false;  // x += alpha p of the last iteration not yet applied
-  // two-scale P with a coarse space: the update of r also restricts it, and
-  // the coarse solve starts beside the convergence check and the patch solves
-  const bool fused = pc == SEM_PC_TWOSCALE && m->T.nc > 0 && !m->in_capture;
-  bool coarse_pending = false;
-  // speculative ordering of the convergence check: needs the pinned read-back
-  // buffer (made by an ordinary solve's set-up; not in the allocation-free one)
-  const bool spec_ok = m->check_host != nullptr && m->ev_check != nullptr;
-  while (k < max_iter) {
-    apply_A_dot<T>(m, p, w, 1, 1, s);
-    if (fused) {
-      update_r_and_fork_coarse<T>(m, r, (const T*)w, s);
-      coarse_pending = true;
-    } else {
-      hipLaunchKernelGGL((update_r_kernel<T>), dim3(nb), dim3(kRedThreads), 0, s, r, (const T*)w, (const double*)sc,
-                         m->wk.part, n, (int)aligned16(r, w));
-      SEM_HIP(hipGetLastError());
-      hipLaunchKernelGGL(dot_final_kernel, dim3(1), dim3(kRedThreads), 0, s, m->wk.part, sc, nb, 4, 0);
+  SEM_HIP(hipGetLastError());
+  int rz = 0, rz_next = 10;  // scalar slots of r . z, in turn
+  if (pc == SEM_PC_NONE) {
+    hipLaunchKernelGGL((copy_kernel<T, T>), dim3(gb), dim3(kGS), 0, s, p, (const T*)r, n);
+    SEM_HIP(hipGetLastError());
+    dot<T, T>(m, r, r, rz, s);
+  } else {
+    if (coarse) {
+      launch_restrict<T>(m, r, s);
+      pcg_start_coarse(m, fine, s);
     }
+    pcg_finish<T>(m, r, x, p, fine, coarse, rz, rz, true, s);
+  }
+  int status = SEM_ENOCONV;
+  bool pending_x = false;       // x += alpha p of the last iteration not yet applied
+  bool coarse_pending = false;  // a coarse solve forked that no pcg_finish has joined
+  int late = 0;                 // iteration whose check is not looked at yet (0: none)
+  // r . r of iteration q, read back by its check; true when the solve is over
+  auto over = [&](int q) {
+    SEM_HIP(hipEventSynchronize(m->ev_check[q & 1]));
+    const double* h = m->check_host + 2 * (q & 1);
+    rr = h[0];
+    const double flag = h[1];
+    if (st && st->history && st->history_len < st->history_cap)
+      st->history[st->history_len++] = std::sqrt(rr / bnorm2);
+    if (flag != 0.0 || !std::isfinite(rr))
+      status = SEM_EBREAKDOWN;
+    else if (rr <= tol2)
+      status = SEM_OK;
+    else
+      return false;
+    k = q;
+    return true;
+  };
+  while (k < max_iter) {
+    const int64_t nr = pcg_update_r<T>(m, r, p, w, rz, coarse, s);
     ++k;
     pending_x = true;
-    bool z_ready = false;  // the preconditioner of this step already enqueued
-    if (k % check_every == 0 || k == max_iter) {
-      // r^T r (slot 4) and the breakdown flag (slot 6) in one read-back.  Far
-      // from the tolerance (the last r^T r above 100 tol^2) the step's
-      // preconditioner is enqueued before the host waits for them, so the GPU
-      // works through the round trip; if the check then ends the solve, that
-      // preconditioner was spent for nothing, which this margin makes rare
-      double sc46[3];
-      if (spec_ok && k < max_iter && rr > 100.0 * tol2) {
-        SEM_HIP(hipMemcpyAsync(m->check_host, sc + 4, sizeof(sc46), hipMemcpyDeviceToHost, s));
-        SEM_HIP(hipEventRecord(m->ev_check, s));
-        precond_dot<T>(m, r, z, pc, 5, 2, s, coarse_pending);
-        coarse_pending = false;
-        z_ready = true;
-        SEM_HIP(hipEventSynchronize(m->ev_check));
-        std::memcpy(sc46, m->check_host, sizeof(sc46));
-      } else {
-        SEM_HIP(hipMemcpyAsync(sc46, sc + 4, sizeof(sc46), hipMemcpyDeviceToHost, s));
-        SEM_HIP(hipStreamSynchronize(s));
-      }
-      rr = sc46[0];
-      const double flag = sc46[2];
-      if (st && st->history && st->history_len < st->history_cap)
-        st->history[st->history_len++] = std::sqrt(rr / bnorm2);
-      if (flag != 0.0 || !std::isfinite(rr)) {
-        status = SEM_EBREAKDOWN;
-        break;
-      }
-      if (rr <= tol2) {
-        status = SEM_OK;
+    const bool check = k % check_every == 0 || k == max_iter;
+    if (pc == SEM_PC_NONE) reduce_partials(m, m->wk.rpart, nr, 5, 2, s, rz, rz_next);
+    if (check) {
+      reduce_partials(m, m->wk.rpart, nr, 4, 3, s, 0, 0, m->check_host + 2 * (k & 1));
+      SEM_HIP(hipEventRecord(m->ev_check[k & 1], s));
+    }
+    if (coarse) {
+      pcg_start_coarse(m, fine, s);
+      coarse_pending = fine && coarse_beside(m);
+    }
+    // The check of the iteration before, then this one's.  Far from the
+    // tolerance (the last r . r above 100 tol^2) this one's is looked at when
+    // the next iteration's first half is enqueued, so that the GPU works
+    // through the host's round trip; if it then ends the solve, x is already
+    // the iterate of this step, and what follows it was spent for nothing,
+    // which this margin makes rare
+    if (late != 0) {
+      const int q = late;
+      late = 0;
+      if (over(q)) {
+        pending_x = false;  // applied before the next iteration began
         break;
       }
     }
-    if (!z_ready) {
-      precond_dot<T>(m, r, z, pc, 5, 2, s, coarse_pending);
+    if (check) {
+      if (k < max_iter && rr > 100.0 * tol2)
+        late = k;
+      else if (over(k))
+        break;
+    }
+    if (pc == SEM_PC_NONE) {
+      hipLaunchKernelGGL((update_px_kernel<T>), dim3(gb), dim3(kGS), 0, s, x, p, (const T*)r, (const double*)sc, n,
+                         (int)aligned16(x, p, r));
+      SEM_HIP(hipGetLastError());
+    } else {
+      pcg_finish<T>(m, r, x, p, fine, coarse, rz, rz_next, false, s);
       coarse_pending = false;
     }
-    hipLaunchKernelGGL((update_px_kernel<T>), dim3(gb), dim3(kGS), 0, s, x, p, (const T*)z, (const double*)sc, n,
-                       (int)aligned16(x, p, z));
-    SEM_HIP(hipGetLastError());
+    std::swap(rz, rz_next);
     pending_x = false;
   }
   // a coarse solve forked for an iteration that did not follow: the caller's
@@ -1301,8 +1388,7 @@ int solve_impl(sem_mesh m, const double* b, double* x, const sem_solve_opts* o, 
   auto residual = [&](const double* ax, int slot) {
     hipLaunchKernelGGL(residual_kernel, dim3(nb), dim3(kRedThreads), 0, s, r64, b, ax, (const uint8_t*)m->dir.p,
                        m->wk.part, n);
-    hipLaunchKernelGGL(dot_final_kernel, dim3(1), dim3(kRedThreads), 0, s, m->wk.part, m->wk.sc, nb, slot, 0);
-    SEM_HIP(hipGetLastError());
+    reduce_partials(m, m->wk.part, nb, slot, 0, s);
     return read_scalar(m, slot, s);
   };
   const double bnorm2 = residual(nullptr, 7);
@@ -1373,7 +1459,7 @@ int solve_impl(sem_mesh m, const double* b, double* x, const sem_solve_opts* o, 
       hipLaunchKernelGGL((fill_kernel<float>), dim3(gb), dim3(kGS), 0, s, d32, 0.0f, n);
       SEM_HIP(hipGetLastError());
       // ||r32||^2 of the scaled residual (about 1)
-      dot<float, float>(m, r32, r32, 9, 0, s);
+      dot<float, float>(m, r32, r32, 9, s);
       const double r32n2 = read_scalar(m, 9, s);
       int it = 0;
       double irel = 0.0;
@@ -1622,7 +1708,8 @@ int sem_mesh_destroy(sem_mesh m) {
     if (m->side_stream) (void)hipStreamDestroy(m->side_stream);
     if (m->ev_fork) (void)hipEventDestroy(m->ev_fork);
     if (m->ev_join) (void)hipEventDestroy(m->ev_join);
-    if (m->ev_check) (void)hipEventDestroy(m->ev_check);
+    for (auto e : m->ev_check)
+      if (e) (void)hipEventDestroy(e);
     if (m->check_host) (void)hipHostFree(m->check_host);
   }
   delete m;
@@ -1754,9 +1841,9 @@ int sem_time_apply_A(sem_mesh m, const void* u, void* y, int dtype, int reps, vo
         apply_A_elements<float>(m, (const float*)u, (float*)y, s);
       SEM_HIP(hipEventRecord(ev[3 * r + 1], s));
       if (dtype == SEM_F64)
-        launch_gs<double>(m, (double*)y, s, nullptr, nullptr, (const double*)u);
+        launch_gs<double>(m, (double*)y, s, (const double*)u);
       else
-        launch_gs<float>(m, (float*)y, s, nullptr, nullptr, (const float*)u);
+        launch_gs<float>(m, (float*)y, s, (const float*)u);
       SEM_HIP(hipEventRecord(ev[3 * r + 2], s));
     }
     SEM_HIP(hipStreamSynchronize(s));

@@ -51,6 +51,20 @@ __device__ __forceinline__ T op_value(const OpCoef<T>& oc, T stiff, int64_t g, T
   return v;
 }
 
+// A node's share of u^T A u from one element: u times the element's own value,
+// so that the scalar product needs no assembled vector (u is 0 on the Dirichlet
+// set, where the operator's result is masked).  With constant coefficients the
+// mass term is added at assembly; the element that owns the node counts it.
+template <typename T>
+__device__ __forceinline__ double local_energy(const OpCoef<T>& oc, T v, T u, int64_t g, bool owned) {
+  double d = (double)u * (double)v;
+  if (oc.scaled) {
+    d *= (double)oc.kap;
+    if (oc.cm != T(0) && owned) d += (double)oc.cm * (double)oc.mN[g] * (double)u * (double)u;
+  }
+  return d;
+}
+
 // element e's kappa_e, c_e (1, 0 without per-element coefficients), read
 // once per element before its results are stored
 template <typename T>
@@ -331,7 +345,7 @@ ax_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, const T
     }
   }
   // interior results straight to y, shared ones to the work array; with dpart,
-  // this workgroup's share of u . y over the interior nodes
+  // this workgroup's share of u^T A u
   double dacc = 0.0;
   if (valid) {
     const bool masked_interior = rec[(e * kClasses + kInteriorClass) * kRecInts + 3] & kFlagMaskedInterior;
@@ -344,12 +358,19 @@ ax_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, const T
       const int off = ai * i + aj * j + ak * k;
       const T uk = ((r.w & kFlagInterior) || oc.ke != nullptr) ? sU[le][k * P + ij] : T(0);
       const T v = elem_value(oc, ec, e, NN, k * P + ij, rw[k], uk);
-      if (r.w & kFlagInterior) {
-        const T yv = (masked_interior && dir[r.x + off]) ? T(0) : op_value(oc, v, r.x + off, uk);
-        y[r.x + off] = yv;
-        dacc += (double)uk * (double)yv;
-      } else {
+      if (r.w & kFlagInterior)
+        y[r.x + off] = (masked_interior && dir[r.x + off]) ? T(0) : op_value(oc, v, r.x + off, uk);
+      else
         w[r.z + off] = v;
+      rw[k] = v;
+    }
+    if (dpart != nullptr) {
+#pragma unroll
+      for (int k = 0; k < n1; ++k) {
+        const int4 r = k == 0 ? r0 : (k == N ? r2 : r1);
+        int ai, aj, ak;
+        unpack_coef(r.y, ai, aj, ak);
+        dacc += local_energy(oc, rw[k], sU[le][k * P + ij], r.x + ai * i + aj * j + ak * k, r.w & kFlagOwned);
       }
     }
   }
@@ -739,12 +760,19 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
       const int off = ai * a + aj * b + ak * k;
       const T uk = uv[k];
       const T v = elem_value(oc, ec, e, NN, k * P + ij, rw[k], uk);
-      if (r.w & kFlagInterior) {
-        const T yv = (masked_interior && dir[r.x + off]) ? T(0) : op_value(oc, v, r.x + off, uk);
-        y[r.x + off] = yv;
-        dacc += (double)uk * (double)yv;
-      } else {
+      if (r.w & kFlagInterior)
+        y[r.x + off] = (masked_interior && dir[r.x + off]) ? T(0) : op_value(oc, v, r.x + off, uk);
+      else
         w[r.z + off] = v;
+      rw[k] = v;
+    }
+    if (dpart != nullptr) {
+#pragma unroll
+      for (int k = 0; k < n1; ++k) {
+        const int4 r = k == 0 ? q0 : (k == N ? q2 : q1);
+        int ai, aj, ak;
+        unpack_coef(r.y, ai, aj, ak);
+        dacc += local_energy(oc, rw[k], uv[k], r.x + ai * a + aj * b + ak * k, r.w & kFlagOwned);
       }
     }
   }
@@ -882,7 +910,7 @@ ax_mfma15_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w,
   // 3. zeta transpose and output: tile t = row j of every plane
   const bool masked_interior = rec[(e * kClasses + kInteriorClass) * kRecInts + 3] & kFlagMaskedInterior;
   const ElemCoef<T> ec = elem_coef(oc, e);
-  double dacc = 0.0;  // share of u . y over interior nodes, with dpart
+  double dacc = 0.0;  // share of u^T A u, with dpart
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int t = wave * 4 + q;
@@ -896,13 +924,11 @@ ax_mfma15_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w,
       const NodeAddr a = node_addr(rec, e, cx, cy, k, i, j, N);
       const T ug = (dpart != nullptr || oc.scaled || oc.ke != nullptr) ? u[a.g] : T(0);
       const T v = elem_value(oc, ec, e, NN, k * P + j * n1 + i, acc[r] + sU[k * P + j * n1 + i], ug);
-      if (a.flags & kFlagInterior) {
-        const T yv = (masked_interior && dir[a.g]) ? T(0) : op_value(oc, v, a.g, ug);
-        y[a.g] = yv;
-        if (dpart != nullptr) dacc += (double)ug * (double)yv;
-      } else {
+      if (a.flags & kFlagInterior)
+        y[a.g] = (masked_interior && dir[a.g]) ? T(0) : op_value(oc, v, a.g, ug);
+      else
         w[a.w] = v;
-      }
+      if (dpart != nullptr) dacc += local_energy(oc, v, ug, a.g, a.flags & kFlagOwned);
     }
   }
   if (dpart != nullptr) {
@@ -914,44 +940,121 @@ ax_mfma15_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w,
 
 // ---------------------------------------------------------------------------
 // Gather of the shared nodes (eq. (gather)): one lane per shared global node,
-// copies summed in ascending element order, Dirichlet nodes zeroed.  As the
-// operator's last step (oc.scaled) it also applies kappa and the mass term at
-// the shared nodes of u; as the preconditioner's assembly it only sums.
+// copies summed in ascending element order.
 // ---------------------------------------------------------------------------
+struct SharedNodes {
+  const int32_t *vinc_off, *einc_off;
+  const uint8_t *fcount, *dir;
+  int64_t V, base_f, base_i;  // vertices, first face node, first interior node
+  int m;                      // N - 1
+  int64_t wedge_off, wvert_off;
+};
+
+template <typename T>
+__device__ __forceinline__ T shared_sum(const T* __restrict__ w, const SharedNodes& sn, int64_t g) {
+  T s = 0;
+  if (g >= sn.base_f) {  // face node (most shared nodes): both slots read, the second kept on interior faces
+    const uint32_t mm = (uint32_t)sn.m * (uint32_t)sn.m, q = (uint32_t)(g - sn.base_f), f = q / mm, r = q - f * mm;
+    const T s0 = w[2 * (int64_t)f * mm + r], s1 = w[(2 * (int64_t)f + 1) * mm + r];
+    s = sn.fcount[f] == 2 ? s0 + s1 : s0;
+  } else if (g < sn.V) {
+    for (int32_t q = sn.vinc_off[g]; q < sn.vinc_off[g + 1]; ++q) s += w[sn.wvert_off + q];
+  } else {
+    const uint32_t q = (uint32_t)(g - sn.V), ed = q / (uint32_t)sn.m, r = q - ed * (uint32_t)sn.m;
+    for (int32_t x = sn.einc_off[ed]; x < sn.einc_off[ed + 1]; ++x) s += w[sn.wedge_off + (int64_t)x * sn.m + r];
+  }
+  return s;
+}
+
+// Dirichlet nodes zeroed.  As the operator's last step (oc.scaled) it also
+// applies kappa and the mass term at the shared nodes of u; as the
+// preconditioner's assembly it only sums.
 template <typename T>
 __global__ void __launch_bounds__(256)
-gs_kernel(T* __restrict__ y, const T* __restrict__ w, const int32_t* __restrict__ vinc_off,
-          const int32_t* __restrict__ einc_off, const uint8_t* __restrict__ fcount,
-          const uint8_t* __restrict__ dir, int64_t V, int64_t base_f, int64_t base_i, int m,
-          int64_t wedge_off, int64_t wvert_off, const T* __restrict__ pd, double* __restrict__ dpart,
-          OpCoef<T> oc, const T* __restrict__ u) {
+gs_kernel(T* __restrict__ y, const T* __restrict__ w, SharedNodes sn, OpCoef<T> oc, const T* __restrict__ u) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  double d = 0.0;
-  if (g < base_i) {
-    // every load of the node issued before any is used (node ids fit in 32 bits)
-    const uint8_t dg = dir[g];
-    const T pg = dpart != nullptr ? pd[g] : T(0);
-    T s = 0;
-    if (g >= base_f) {  // face node (most shared nodes): both slots read, the second kept on interior faces
-      const uint32_t mm = (uint32_t)m * (uint32_t)m, q = (uint32_t)(g - base_f), f = q / mm, r = q - f * mm;
-      const T s0 = w[2 * (int64_t)f * mm + r], s1 = w[(2 * (int64_t)f + 1) * mm + r];
-      s = fcount[f] == 2 ? s0 + s1 : s0;
-    } else if (g < V) {
-      for (int32_t q = vinc_off[g]; q < vinc_off[g + 1]; ++q) s += w[wvert_off + q];
-    } else {
-      const uint32_t q = (uint32_t)(g - V), ed = q / (uint32_t)m, r = q - ed * (uint32_t)m;
-      for (int32_t x = einc_off[ed]; x < einc_off[ed + 1]; ++x) s += w[wedge_off + (int64_t)x * m + r];
+  if (g >= sn.base_i) return;
+  const uint8_t dg = sn.dir[g];  // issued with the slots' loads
+  const T s = shared_sum(w, sn, g);
+  y[g] = dg ? T(0) : op_value(oc, s, g, oc.scaled ? u[g] : T(0));
+}
+
+// PCG's last step at the shared nodes: z gathered from the work array, then
+// x += alpha p and p = z + beta p (schwarz_sum_kernel does the interiors), so
+// that z is never stored.  start: p = z alone.
+template <typename T>
+__global__ void __launch_bounds__(256)
+gs_px_kernel(T* __restrict__ x, T* __restrict__ p, const T* __restrict__ w, SharedNodes sn,
+             const double* __restrict__ sc, int start) {
+  if (sc[6] != 0.0) return;  // whole grid
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= sn.base_i) return;
+  const T al = (T)sc[2], beta = (T)sc[3];
+  const uint8_t dg = sn.dir[g];
+  T pg = 0, xg = 0;
+  if (!start) {
+    pg = p[g];
+    xg = x[g];
+  }
+  const T s = shared_sum(w, sn, g);
+  const T z = dg ? T(0) : s;
+  if (start) {
+    p[g] = z;
+  } else {
+    x[g] = xg + al * pg;
+    p[g] = z + beta * pg;
+  }
+}
+
+// sum of n partial sums by every workgroup of a consuming kernel (one wave or
+// more, any size): the same order, so the same value, in each
+template <int NT>
+__device__ __forceinline__ double all_partials(const double* __restrict__ part, int n, double* red) {
+  constexpr int W = (NT + 63) / 64;
+  double s = 0.0;
+  for (int q = threadIdx.x; q < n; q += NT) s += part[q];
+  // lanes past the workgroup's end count as zero
+  for (int o = 32; o > 0; o >>= 1) {
+    const double t = __shfl_xor(s, o);
+    s += ((int)(threadIdx.x ^ o) < NT) ? t : 0.0;
+  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  double t = 0.0;
+#pragma unroll
+  for (int q = 0; q < W; ++q) t += red[q];
+  __syncthreads();
+  return t;
+}
+
+// PCG's r -= alpha A p at the shared nodes: A p gathered from the work array
+// (with the coefficients, as gs_kernel; u = p), not stored.  alpha comes from
+// sc[2], or, with na > 0, from the na partial sums of p . A p (every workgroup
+// sums them; block 0 also stores the scalars).
+template <typename T>
+__global__ void __launch_bounds__(256)
+gs_r_kernel(T* __restrict__ r, const T* __restrict__ w, SharedNodes sn, OpCoef<T> oc, const T* __restrict__ u,
+            double* __restrict__ sc, int rz, const double* __restrict__ apart, int na) {
+  __shared__ double sRed[256 / 64];
+  T al;
+  if (na > 0) {
+    const double t = all_partials<256>(apart, na, sRed), a = sc[rz] / t;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      sc[1] = t;
+      sc[2] = a;
+      if (!(t > 0.0) || !isfinite(a)) sc[6] = 1.0;
     }
-    const T yv = dg ? T(0) : op_value(oc, s, g, oc.scaled ? u[g] : T(0));
-    y[g] = yv;
-    if (dpart != nullptr) d = (double)pg * (double)yv;
+    al = (T)a;
+  } else {
+    al = (T)sc[2];
   }
-  // with dpart: this workgroup's share of pd . y over the shared nodes
-  if (dpart != nullptr) {
-    __shared__ double red[256 / 64];
-    const double t = group_sum<256>(d, red);
-    if (threadIdx.x == 0) dpart[blockIdx.x] = t;
-  }
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= sn.base_i) return;
+  const uint8_t dg = sn.dir[g];
+  const T rg = r[g];
+  const T s = shared_sum(w, sn, g);
+  const T Ap = dg ? T(0) : op_value(oc, s, g, oc.scaled ? u[g] : T(0));
+  r[g] = rg - al * Ap;
 }
 
 // ---------------------------------------------------------------------------
@@ -1040,15 +1143,19 @@ __global__ void __launch_bounds__(fdm_threads<N>()) __attribute__((amdgpu_waves_
 fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, const int32_t* __restrict__ ip,
            const int32_t* __restrict__ xdest, const T* __restrict__ S,
            const T* __restrict__ lam, const T* __restrict__ hg, const int32_t* __restrict__ order, int64_t E,
-           T kap, T cm, const T* __restrict__ ke, const T* __restrict__ ce) {
+           T kap, T cm, const T* __restrict__ ke, const T* __restrict__ ce, double* __restrict__ epart) {
   constexpr int m = N + 3, MM = m * m, MMM = MM * m, PPB = fdm_ppb<N>(), NT = fdm_threads<N>();
   constexpr int NN = (N + 1) * (N + 1) * (N + 1), NX = MMM - NN, R = (PPB * MMM + NT - 1) / NT;
   __shared__ T X[PPB * MMM];
   __shared__ T sL[m];
   __shared__ int64_t sE[PPB];  // element of each patch slot, -1 past the end
+  __shared__ double sRed[NT / 64];
   const int tid = threadIdx.x;
   const int64_t pos0 = xcd_position(blockIdx.x, (E + PPB - 1) / PPB) * PPB;
-  if (pos0 >= E) return;  // whole workgroup
+  if (pos0 >= E) {  // whole workgroup
+    if (epart != nullptr && tid == 0) epart[blockIdx.x] = 0.0;
+    return;
+  }
   if (tid < PPB) sE[tid] = pos0 + tid < E ? (int64_t)order[pos0 + tid] : -1;
   if (tid < m) sL[tid] = lam[tid];
   __syncthreads();
@@ -1091,7 +1198,10 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
     for (int b = 0; b < m; ++b) col[b * m] = o[b];
   }
   __syncthreads();
-  // pass 3: zeta, S^T, diagonal, S  (lane owns pencil (a = p0, b = p1))
+  // pass 3: zeta, S^T, diagonal, S  (lane owns pencil (a = p0, b = p1)); with
+  // epart, the workgroup's share of r . z: with y = S^T r the transformed
+  // residual, r_s . z_s = 8/(hx hy hz) sum y^2 / diagonal, all in registers here
+  double en = 0.0;
   if (act) {
     const T hx = hg[e * 3 + 0], hy = hg[e * 3 + 1], hz = hg[e * 3 + 2];
     const T ihx2 = T(4) / (hx * hx), ihy2 = T(4) / (hy * hy), ihz2 = T(4) / (hz * hz);
@@ -1104,10 +1214,29 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
     const T dab = sL[p0] * ihx2 + sL[p1] * ihy2;
     pencil_St<m, T>(S, pen, MM, o);
 #pragma unroll
-    for (int c = 0; c < m; ++c) o[c] = o[c] * recip_pos(kp * (dab + sL[c] * ihz2) + c0);
+    for (int c = 0; c < m; ++c) {
+      const T yc = o[c];
+      o[c] = yc * recip_pos(kp * (dab + sL[c] * ihz2) + c0);
+      if (epart != nullptr) en += (double)yc * (double)o[c];
+    }
+    if (epart != nullptr) {  // the sizes read again (cached): held through the pass they would spill
+      int64_t eh = e;
+      asm volatile("" : "+v"(eh));
+      en *= 8.0 / ((double)hg[eh * 3] * (double)hg[eh * 3 + 1] * (double)hg[eh * 3 + 2]);
+    }
     pencil_S<m, T>(S, o, pen, MM, T(1));
   }
+  if (epart != nullptr) {
+    for (int q = 32; q > 0; q >>= 1) en += __shfl_xor(en, q);
+    if ((tid & 63) == 0) sRed[tid >> 6] = en;
+  }
   __syncthreads();
+  if (epart != nullptr && tid == 0) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < NT / 64; ++q) t += sRed[q];
+    epart[blockIdx.x] = t;
+  }
   // pass 4: eta, S
   if (act) {
     T* col = Xp + p1 * MM + p0;
@@ -1188,28 +1317,53 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
 // walks its k-pencil: the patch of e itself (zc) plus the corrections that the
 // neighbouring patches left in e's consumer layout (zx: planes one layer in
 // from each face, lines one layer in from both faces of each edge, corner
-// points), then I Z at the nodes e owns.  Element interiors go straight to z
-// (Dirichlet zeroed), shared nodes to the work array for gs_kernel.  With
-// dpart, each workgroup also leaves its share of rd . z over the interior
-// nodes (the gather adds the shared nodes' share), so that PCG's r . z needs
-// no pass of its own.
+// points), then I Z at the nodes e owns.  Shared nodes go to the work array for
+// the gather; element interiors (Dirichlet zeroed)
+//   kSumZ:     straight to z;
+//   kSumStart: to p (the first search direction);
+//   kSumPx:    into PCG's updates x += alpha p, p = z + beta p, so that z is
+//              never stored: beta is known before this kernel, since r . z is
+//              the patch solves' and the coarse solve's energies.  beta comes
+//              from sc[3], or, with nb > 0, from the nb partial sums themselves
+//              (every workgroup sums them; block 0 also stores the scalars).
 // ---------------------------------------------------------------------------
-template <int N, typename T, int EPB>
+enum : int { kSumZ = 0, kSumStart = 1, kSumPx = 2 };
+
+template <int N, typename T, int EPB, int MODE>
 __global__ void __launch_bounds__(EPB*(N + 1) * (N + 1))
-schwarz_sum_kernel(T* __restrict__ z, T* __restrict__ w, const T* __restrict__ zc, const T* __restrict__ zx,
-                   const int32_t* __restrict__ rec, const uint8_t* __restrict__ dir,
+schwarz_sum_kernel(T* __restrict__ z, T* __restrict__ x, T* __restrict__ w, const T* __restrict__ zc,
+                   const T* __restrict__ zx, const int32_t* __restrict__ rec, const uint8_t* __restrict__ dir,
                    const int32_t* __restrict__ order, int64_t E, int use_fine, const double* __restrict__ Zv,
-                   const double* __restrict__ phi, const T* __restrict__ rd, double* __restrict__ dpart) {
+                   const double* __restrict__ phi, double* __restrict__ sc, int rz_in, int rz_out,
+                   const double* __restrict__ bpart, int nb) {
   constexpr int n1 = N + 1, P = n1 * n1, NN = P * n1;
   constexpr int NX = (N + 3) * (N + 3) * (N + 3) - NN;
   constexpr int F0 = 0, E0 = 6 * P, C0 = 6 * P + 12 * n1;
   constexpr int RX = (NX + P - 1) / P;
   __shared__ T sX[EPB][NX];  // the element's consumer layout, staged with coalesced loads
   __shared__ double sPhi[2 * n1];
-  __shared__ double sRed[EPB * P];
+  __shared__ double sRed[(EPB * P + 63) / 64];
   const int tid = threadIdx.x;
   const int le = tid / P, ij = tid - le * P;
   const int i = ij % n1, j = ij / n1;
+  T al = 0, beta = 0;
+  if constexpr (MODE == kSumPx) {
+    if (sc[6] != 0.0) return;  // whole grid
+    if (nb > 0) {
+      const double t = all_partials<EPB * P>(bpart, nb, sRed);
+      const double bd = t / sc[rz_in];
+      if (blockIdx.x == 0 && tid == 0) {
+        sc[3] = bd;
+        sc[rz_out] = t;
+        if (!isfinite(bd)) sc[6] = 1.0;
+      }
+      if (!isfinite(bd)) return;  // every workgroup alike
+      beta = (T)bd;
+    } else {
+      beta = (T)sc[3];
+    }
+    al = (T)sc[2];
+  }
   const int64_t pos = xcd_position(blockIdx.x, (E + EPB - 1) / EPB) * EPB + le;
   const bool valid = pos < E;
   const int64_t e = valid ? order[pos] : 0;
@@ -1230,15 +1384,18 @@ schwarz_sum_kernel(T* __restrict__ z, T* __restrict__ w, const T* __restrict__ z
     for (int q = 0; q < RX; ++q)
       if (ij + q * P < NX) sX[le][ij + q * P] = xv[q];
   }
-  // with dpart: rd at the lane's interior nodes (1 <= k < N), loaded ahead of
+  // kSumPx: p and x at the lane's interior nodes (1 <= k < N), loaded ahead of
   // the sum so that the loop's loads do not wait one by one
-  const bool int_ij = (r1.w & kFlagInterior) != 0;
-  T rdk[n1];
-  if (dpart != nullptr && valid && int_ij) {
+  T pk[n1], xk[n1];
+  if (MODE == kSumPx && valid && (r1.w & kFlagInterior)) {
     int ai, aj, ak;
     unpack_coef(r1.y, ai, aj, ak);
+    const int base = r1.x + ai * i + aj * j;
 #pragma unroll
-    for (int k = 1; k < N; ++k) rdk[k] = rd[r1.x + ai * i + aj * j + ak * k];
+    for (int k = 1; k < N; ++k) {
+      pk[k] = z[base + ak * k];
+      xk[k] = x[base + ak * k];
+    }
   }
   double zv[8];
   if (Zv != nullptr) {
@@ -1263,7 +1420,6 @@ schwarz_sum_kernel(T* __restrict__ z, T* __restrict__ w, const T* __restrict__ z
   }
   const T* xs = sX[le];
   const bool li0 = i == 1, li1 = i == N - 1, lj0 = j == 1, lj1 = j == N - 1;
-  double dacc = 0.0;  // with dpart: this workgroup's share of rd . z over the interior nodes
 #pragma unroll
   for (int k = 0; k < n1; ++k) {
     if (!valid) break;
@@ -1302,16 +1458,18 @@ schwarz_sum_kernel(T* __restrict__ z, T* __restrict__ w, const T* __restrict__ z
     unpack_coef(rr.y, ai, aj, ak);
     const int off = ai * i + aj * j + ak * k;
     if (rr.w & kFlagInterior) {
-      const T zv = (masked_interior && dir[rr.x + off]) ? T(0) : v;
-      z[rr.x + off] = zv;
-      if (dpart != nullptr && k > 0 && k < N) dacc += (double)rdk[k] * (double)zv;
+      const T zk = (masked_interior && dir[rr.x + off]) ? T(0) : v;
+      if constexpr (MODE == kSumPx) {
+        if (k > 0 && k < N) {  // always, at an interior node
+          x[rr.x + off] = xk[k] + al * pk[k];
+          z[rr.x + off] = zk + beta * pk[k];
+        }
+      } else {
+        z[rr.x + off] = zk;
+      }
     } else {
       w[rr.z + off] = v;
     }
-  }
-  if (dpart != nullptr) {
-    const double t = group_sum<EPB * P>(dacc, sRed);
-    if (tid == 0) dpart[blockIdx.x] = t;
   }
 }
 
@@ -1377,31 +1535,36 @@ restrict_kernel(const T* __restrict__ r, double* __restrict__ cvec, const int32_
   }
 }
 
-// r -= alpha w at the nodes each element owns (each global node once), with
-// the element's part of the coarse restriction of the updated r (as
-// restrict_kernel) and of r . r (dpart[block], 0 for the padding blocks).  Lets the coarse chain start right after the update
-// of r, before the patch solves.
-template <int N, typename T>
-__global__ void __launch_bounds__((N + 1) * (N + 1))
-update_r_restrict_kernel(T* __restrict__ r, const T* __restrict__ w, const double* __restrict__ sc,
-                         double* __restrict__ cvec, const int32_t* __restrict__ part_dst, double* __restrict__ dpart,
-                         const int32_t* __restrict__ rec, const double* __restrict__ phi,
-                         const int32_t* __restrict__ order, int64_t E) {
+// r -= alpha A p, second half (gs_r_kernel has done the shared nodes): the
+// interiors of each element, A p from y, and over the nodes that the element owns
+// (each global node once) the workgroup's share of r . r (rpart[block], 0 for the
+// padding blocks) and, with cvec, the element's part of the coarse restriction of
+// the updated r (as restrict_kernel).  Lets the coarse chain start right after
+// the update of r, before the patch solves.  (All in one kernel, the owner
+// summing the copies of its shared nodes, measured 69 against 40 us at 24^3,
+// N = 7: 140 VGPRs and a serial tail at edges and vertices.)
+template <int N, typename T, int EPB>
+__global__ void __launch_bounds__(EPB*(N + 1) * (N + 1))
+update_r_kernel(T* __restrict__ r, const T* __restrict__ y, const double* __restrict__ sc, double* __restrict__ cvec,
+                const int32_t* __restrict__ part_dst, double* __restrict__ rpart, const int32_t* __restrict__ rec,
+                const double* __restrict__ phi, const int32_t* __restrict__ order, int64_t E) {
   constexpr int n1 = N + 1, P = n1 * n1;
-  __shared__ double red[9][P + 1];  // padded rows: the summing lanes read distinct banks
+  __shared__ double red[EPB][9][P + 1];  // padded rows: the summing lanes read distinct banks
   __shared__ double sPhi[2 * n1];
   const int tid = threadIdx.x;
-  const int i = tid % n1, j = tid / n1;
-  const int64_t pos = xcd_position(blockIdx.x, E);
+  const int le = tid / P, ij = tid - le * P;
+  const int i = ij % n1, j = ij / n1;
+  const int64_t pos = xcd_position(blockIdx.x, (E + EPB - 1) / EPB) * EPB + le;
   const bool valid = pos < E;
   const int64_t e = valid ? order[pos] : 0;
-  for (int x = tid; x < 2 * n1; x += P) sPhi[x] = phi[x];
+  for (int x = tid; x < 2 * n1; x += EPB * P) sPhi[x] = phi[x];
   const int cx = node_class(i, N), cy = node_class(j, N);
   const int4* rp = reinterpret_cast<const int4*>(rec) + e * kClasses + cx + 3 * cy;
   const int4 r0 = rp[0], r1 = rp[9], r2 = rp[18];
   const T al = (T)sc[2];
+  const bool in = r1.w & kFlagInterior;  // the lane's nodes 1 <= k < N
   T rv[n1], wv[n1];
-  int32_t gk[n1];  // global node ids fit in 32 bits
+  int32_t gk[n1];  // global node ids fit in 32 bits; -1: not owned
 #pragma unroll
   for (int k = 0; k < n1; ++k) {
     const int4 rr = k == 0 ? r0 : (k == N ? r2 : r1);
@@ -1410,7 +1573,7 @@ update_r_restrict_kernel(T* __restrict__ r, const T* __restrict__ w, const doubl
     const bool own = valid && (rr.w & kFlagOwned);
     gk[k] = own ? rr.x + ai * i + aj * j + ak * k : -1;
     rv[k] = own ? r[gk[k]] : T(0);
-    wv[k] = own ? w[gk[k]] : T(0);
+    wv[k] = own && in && k > 0 && k < N ? y[gk[k]] : T(0);
   }
   __syncthreads();
   // restriction as in restrict_kernel: two k-sums per lane, corner weights at the end
@@ -1419,7 +1582,7 @@ update_r_restrict_kernel(T* __restrict__ r, const T* __restrict__ w, const doubl
   for (int k = 0; k < n1; ++k) {
     if (gk[k] < 0) continue;
     const T rn = rv[k] - al * wv[k];
-    r[gk[k]] = rn;
+    if (in && k > 0 && k < N) r[gk[k]] = rn;
     const double v = (double)rn;
     rsq += v * v;
     sk0 += sPhi[k] * v;
@@ -1427,25 +1590,38 @@ update_r_restrict_kernel(T* __restrict__ r, const T* __restrict__ w, const doubl
   }
 #pragma unroll
   for (int c = 0; c < 8; ++c)
-    red[c][tid] = sPhi[(c & 1) * n1 + i] * sPhi[((c >> 1) & 1) * n1 + j] * ((c >> 2) ? sk1 : sk0);
-  red[8][tid] = rsq;
+    red[le][c][ij] = sPhi[(c & 1) * n1 + i] * sPhi[((c >> 1) & 1) * n1 + j] * ((c >> 2) ? sk1 : sk0);
+  red[le][8][ij] = rsq;
   __syncthreads();
-  if (tid < 9) {
+  for (int q = tid; q < 9 * EPB; q += EPB * P) {
+    const int l = q / 9, c = q - 9 * l;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     int x = 0;
     for (; x + 3 < P; x += 4) {
-      s0 += red[tid][x];
-      s1 += red[tid][x + 1];
-      s2 += red[tid][x + 2];
-      s3 += red[tid][x + 3];
+      s0 += red[l][c][x];
+      s1 += red[l][c][x + 1];
+      s2 += red[l][c][x + 2];
+      s3 += red[l][c][x + 3];
     }
-    for (; x < P; ++x) s0 += red[tid][x];
+    for (; x < P; ++x) s0 += red[l][c][x];
     const double t = (s0 + s1) + (s2 + s3);
-    if (tid == 8) {
-      dpart[blockIdx.x] = t;
-    } else if (valid) {
-      const int32_t d = part_dst[e * 8 + tid];
+    if (c == 8) {
+      if constexpr (EPB == 1)
+        rpart[blockIdx.x] = t;
+      else
+        red[l][8][P] = t;
+    } else if (cvec != nullptr && pos - le + l < E) {
+      const int32_t d = part_dst[(int64_t)order[pos - le + l] * 8 + c];
       if (d >= 0) cvec[d] = -t;
+    }
+  }
+  if constexpr (EPB > 1) {
+    __syncthreads();
+    if (tid == 0) {
+      double t = 0.0;
+#pragma unroll
+      for (int l = 0; l < EPB; ++l) t += red[l][8][P];
+      rpart[blockIdx.x] = t;
     }
   }
 }
@@ -1608,14 +1784,15 @@ __device__ __forceinline__ void coarse_tile_dots(const CoarseTile& t, const doub
 // The lowest launch has further workgroups (from n_tiles on) that sum the
 // element parts of the rows of all higher nodes into those rows' first
 // entries, so that the tiles above, each of which assembles its whole node,
-// read one entry instead of eight.
+// read one entry instead of eight.  With epart, each tile also leaves its share
+// of R . Z, which by the block factorisation is the sum of y_t . S_t^-1 y_t.
 template <int RW, bool NARROW>
 __global__ void __launch_bounds__(256)
 coarse_fwd_kernel(double* __restrict__ X, double* __restrict__ Zv, double* __restrict__ cvec,
                   const double* __restrict__ pool, const CoarseTile* __restrict__ tiles,
                   const int32_t* __restrict__ rs_off, const int32_t* __restrict__ cdst,
                   const int32_t* __restrict__ cvert, int n_tiles, const int32_t* __restrict__ pre_slot,
-                  const int32_t* __restrict__ pre_row, int n_pre) {
+                  const int32_t* __restrict__ pre_row, int n_pre, double* __restrict__ epart) {
   __shared__ __attribute__((aligned(16))) double sv[NARROW ? 128 : kCoarseStage];
   if ((int)blockIdx.x >= n_tiles) {
     const int x = ((int)blockIdx.x - n_tiles) * 256 + (int)threadIdx.x;
@@ -1640,15 +1817,25 @@ coarse_fwd_kernel(double* __restrict__ X, double* __restrict__ Zv, double* __res
   });
   const double v = wave_rows_sum<RW>(acc);
   const int r = r0 + lane / (64 / RW);
-  if (lane % (64 / RW) != 0 || r >= t.rows) return;
-  if (r < t.s) {
-    X[t.off + r] = v;
-    if (t.root) Zv[cvert[t.off + r]] = v;
-  } else {
+  double en = 0.0;
+  if (lane % (64 / RW) == 0 && r < t.rows) {
     const int g[1] = {t.src + r};
-    double c[1];
-    row_entries<1, 4>(cvec, rs_off, g, c);
-    cvec[cdst[t.coff + r - t.s]] = v + c[0];
+    double c[1] = {0.0};
+    if (r >= t.s || epart != nullptr) row_entries<1, 8>(cvec, rs_off, g, c);
+    if (r < t.s) {
+      X[t.off + r] = v;
+      if (t.root) Zv[cvert[t.off + r]] = v;
+      en = -c[0] * v;
+    } else {
+      cvec[cdst[t.coff + r - t.s]] = v + c[0];
+    }
+  }
+  if (epart != nullptr) {
+    __shared__ double sp[4];
+    en = wave_sum(en);
+    if (lane == 0) sp[threadIdx.x >> 6] = en;
+    __syncthreads();
+    if (threadIdx.x == 0) epart[blockIdx.x] = ((sp[0] + sp[1]) + sp[2]) + sp[3];
   }
 }
 
@@ -1817,14 +2004,25 @@ amg_in_kernel(double* __restrict__ B0, const double* __restrict__ cvec, const in
   B0[x] = -s;
 }
 
-// vertex-indexed result (0 on Dirichlet vertices) from the level-0 solution
+// vertex-indexed result (0 on Dirichlet vertices) from the level-0 solution;
+// with epart, each workgroup's share of R . Z (B0: the level-0 right-hand side)
 __global__ void __launch_bounds__(256)
-amg_out_kernel(double* __restrict__ Zv, const double* __restrict__ X0, const int32_t* __restrict__ cidx,
-               const int32_t* __restrict__ pos, int64_t V) {
+amg_out_kernel(double* __restrict__ Zv, const double* __restrict__ X0, const double* __restrict__ B0,
+               const int32_t* __restrict__ cidx, const int32_t* __restrict__ pos, int64_t V,
+               double* __restrict__ epart) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= V) return;
-  const int32_t c = cidx[v];
-  Zv[v] = c >= 0 ? X0[pos[c]] : 0.0;
+  double en = 0.0;
+  if (v < V) {
+    const int32_t c = cidx[v];
+    const double z = c >= 0 ? X0[pos[c]] : 0.0;
+    Zv[v] = z;
+    if (epart != nullptr && c >= 0) en = B0[pos[c]] * z;
+  }
+  if (epart != nullptr) {
+    __shared__ double red[256 / 64];
+    const double t = group_sum<256>(en, red);
+    if (threadIdx.x == 0) epart[blockIdx.x] = t;
+  }
 }
 
 // a given coarse residual (vertex order) in place of the element parts: the
@@ -1875,8 +2073,9 @@ __global__ void front_extend_add_kernel(double* __restrict__ F, int64_t f, const
 // ---------------------------------------------------------------------------
 // PCG vector kernels (Algorithm 1).  Reductions are two-pass with a fixed
 // grid and a fixed tree order, so results are reproducible run to run.
-// Scalars live on the device: sc[0] = z^T r, sc[1] = p^T w, sc[2] = alpha,
-// sc[3] = beta, sc[4] = r^T r, sc[5] = scratch, sc[6] = breakdown flag.
+// Scalars live on the device: sc[0] and sc[10] = z^T r of the last two steps in
+// turn, sc[1] = p^T w, sc[2] = alpha, sc[3] = beta, sc[4] = r^T r, sc[6] =
+// breakdown flag.
 // ---------------------------------------------------------------------------
 constexpr int kRedBlocks = 1024;
 constexpr int kRedThreads = 256;
@@ -1932,26 +2131,52 @@ dot_partial_kernel(const TA* __restrict__ a, const TB* __restrict__ b, double* _
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// mode 0: sc[dst] = sum;  mode 1: alpha = sc[0] / sum (p^T w);  mode 2: beta = sum / sc[0], sc[0] = sum
-__global__ void __launch_bounds__(kRedThreads)
-dot_final_kernel(const double* __restrict__ part, double* __restrict__ sc, int nparts, int dst, int mode) {
-  __shared__ double sh[kRedThreads / 64];
-  double s = 0.0;
-  for (int x = threadIdx.x; x < nparts; x += blockDim.x) s += part[x];
-  s = block_sum(s, sh);
-  if (threadIdx.x == 0) {
-    sc[dst] = s;
-    if (mode == 1) {
-      const double a = sc[0] / s;
-      if (!(s > 0.0) || !isfinite(a)) sc[6] = 1.0;
-      sc[2] = a;
-    } else if (mode == 2) {
-      const double bta = s / sc[0];
-      if (!isfinite(bta)) sc[6] = 1.0;
-      sc[3] = bta;
-      sc[0] = s;
+// the scalars of one step of Algorithm 1 from a finished sum
+//   mode 0: sc[dst] = sum;  mode 1: alpha = sc[rz_in] / sum (p^T w);
+//   mode 2: beta = sum / sc[rz_in], sc[rz_out] = sum;
+//   mode 3: sc[4] = sum (r^T r), also to the host with the breakdown flag
+__device__ __forceinline__ void pcg_scalar(double s, double* sc, int dst, int mode, int rz_in, int rz_out,
+                                           double* host) {
+  if (mode == 1) {
+    const double a = sc[rz_in] / s;
+    if (!(s > 0.0) || !isfinite(a)) sc[6] = 1.0;
+    sc[1] = s;
+    sc[2] = a;
+  } else if (mode == 2) {
+    const double bta = s / sc[rz_in];
+    if (!isfinite(bta)) sc[6] = 1.0;
+    sc[3] = bta;
+    sc[rz_out] = s;
+  } else if (mode == 3) {
+    sc[4] = s;
+    if (host != nullptr) {
+      host[0] = s;
+      host[1] = sc[6];
     }
+  } else {
+    sc[dst] = s;
   }
+}
+
+// One workgroup sums up to kOneSum partial sums, 8 loads per lane in flight.
+// (Through chunk sums and a second launch it takes 10 us; alone 5 to 7.)
+constexpr int64_t kOneSum = 65536;
+constexpr int kFinalThreads = 1024;
+__global__ void __launch_bounds__(kFinalThreads)
+dot_final_kernel(const double* __restrict__ part, double* __restrict__ sc, int nparts, int dst, int mode, int rz_in,
+                 int rz_out, double* __restrict__ host) {
+  __shared__ double sh[kFinalThreads / 64];
+  double a[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) a[u] = 0.0;
+  for (int x = threadIdx.x; x < nparts; x += 8 * kFinalThreads)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int q = x + u * kFinalThreads;
+      a[u] += q < nparts ? part[q] : 0.0;
+    }
+  const double s = block_sum(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])), sh);
+  if (threadIdx.x == 0) pcg_scalar(s, sc, dst, mode, rz_in, rz_out, host);
 }
 
 // first stage of a reduction over many partial sums: block b sums the
@@ -1966,49 +2191,11 @@ sum_chunks_kernel(const double* __restrict__ in, double* __restrict__ out, int64
   if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// r -= alpha w; partial sums of r^T r (the matching x update is deferred to
-// update_px_kernel, which reads p anyway)
+// x += alpha p (this iteration's alpha); p = z + beta p: PCG's last step where
+// there is no preconditioner (z = r).  Nothing once the breakdown flag is set (x
+// keeps its last finite iterate).
 // With `pairs`, entries go two at a time (all pointers 16-byte aligned, a
 // single odd tail entry handled by thread 0 of block 0).
-template <typename T>
-__global__ void __launch_bounds__(kRedThreads)
-update_r_kernel(T* __restrict__ r, const T* __restrict__ w, const double* __restrict__ sc, double* __restrict__ part,
-                int64_t n, int pairs) {
-  __shared__ double sh[kRedThreads / 64];
-  typedef typename Pair2<T>::type T2;
-  const T al = (T)sc[2];
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  double s = 0.0;
-  if (pairs) {
-    T2* r2 = reinterpret_cast<T2*>(r);
-    const T2* w2 = reinterpret_cast<const T2*>(w);
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n / 2; q += stride) {
-      const T2 rv = r2[q], wv = w2[q];
-      T2 rn;
-      rn.x = rv.x - al * wv.x;
-      rn.y = rv.y - al * wv.y;
-      r2[q] = rn;
-      s += (double)rn.x * (double)rn.x;
-      s += (double)rn.y * (double)rn.y;
-    }
-    if ((n & 1) && blockIdx.x == 0 && threadIdx.x == 0) {
-      const T rn = r[n - 1] - al * w[n - 1];
-      r[n - 1] = rn;
-      s += (double)rn * (double)rn;
-    }
-  } else {
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += stride) {
-      const T rn = r[q] - al * w[q];
-      r[q] = rn;
-      s += (double)rn * (double)rn;
-    }
-  }
-  s = block_sum(s, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
-}
-
-// x += alpha p (this iteration's alpha); p = z + beta p.  Nothing once the
-// breakdown flag is set (x keeps its last finite iterate).
 template <typename T>
 __global__ void __launch_bounds__(256)
 update_px_kernel(T* __restrict__ x, T* __restrict__ p, const T* __restrict__ z, const double* __restrict__ sc,
