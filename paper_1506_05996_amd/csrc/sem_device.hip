@@ -195,7 +195,7 @@ int64_t launch_ax_tile(sem_mesh m, const T* u, T* y, double* dpart, hipStream_t 
 
 template <int N, typename T, bool GEO, bool KN = false>
 int64_t launch_ax_line(sem_mesh m, const T* u, T* y, double* dpart, hipStream_t s) {
-  constexpr int EPB = ax_epb<N>();
+  constexpr int EPB = line_epb<N>();
   const HostTables& T_ = m->T;
   const int64_t grid = xcd_grid((T_.E + EPB - 1) / EPB);
   hipLaunchKernelGGL((ax_line_kernel<N, T, EPB, GEO, KN>), dim3((unsigned)grid), dim3(EPB * (N + 1) * (N + 1)), 0, s,
@@ -337,7 +337,7 @@ void launch_fdm(sem_mesh m, const T* r, hipStream_t s, double* epart) {
 template <int N, typename T, int MODE>
 void launch_schwarz_sum(sem_mesh m, T* z, T* x, bool fine, const double* Zv, hipStream_t s, int rz_in, int rz_out,
                         const double* bpart, int nb) {
-  constexpr int EPB = ax_epb<N>();
+  constexpr int EPB = sum_epb<N>();
   const T* zc = ZOp<T>(m);
   const T* zx = zc + m->T.E * (int64_t)m->T.n1 * m->T.n1 * m->T.n1;
   hipLaunchKernelGGL((schwarz_sum_kernel<N, T, EPB, MODE>), dim3((unsigned)xcd_grid((m->T.E + EPB - 1) / EPB)),
@@ -361,19 +361,26 @@ void schwarz_sum(sem_mesh m, T* z, T* x, bool fine, const double* Zv, hipStream_
   }
 }
 
-template <int N, typename T>
-void launch_restrict(sem_mesh m, const T* r, hipStream_t s) {
-  hipLaunchKernelGGL((restrict_kernel<N, T>), dim3((unsigned)xcd_grid(m->T.E)), dim3((N + 1) * (N + 1)), 0, s, r,
-                     m->cvec.p, m->part_dst.p, m->rec.p, m->phi.p, m->order.p, m->T.E);
+// the element parts of the coarse residual of r (cvec: into the contribution
+// vector); UPDATE: first r -= alpha A p at the interiors, with r . r.  Returns the
+// number of partial sums of r . r
+template <int N, typename T, bool UPDATE>
+int64_t launch_restrict(sem_mesh m, T* r, const T* y, bool coarse, hipStream_t s) {
+  constexpr int EPB = line_epb<N>();
+  const int64_t grid = xcd_grid((m->T.E + EPB - 1) / EPB);
+  hipLaunchKernelGGL((restrict_kernel<N, T, EPB, UPDATE>), dim3((unsigned)grid), dim3(EPB * (N + 1) * (N + 1)), 0, s,
+                     r, y, (const double*)m->wk.sc, coarse ? m->cvec.p : nullptr, m->part_dst.p, m->wk.rpart, m->rec.p,
+                     (const double*)m->phi.p, m->order.p, m->T.E);
   SEM_HIP(hipGetLastError());
+  return grid;
 }
 
-template <typename T>
-void launch_restrict(sem_mesh m, const T* r, hipStream_t s) {
+template <typename T, bool UPDATE>
+int64_t launch_restrict(sem_mesh m, T* r, const T* y, bool coarse, hipStream_t s) {
   switch (m->T.N) {
 #define CASE(NN) \
   case NN:       \
-    return launch_restrict<NN, T>(m, r, s);
+    return launch_restrict<NN, T, UPDATE>(m, r, y, coarse, s);
     CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14)
     CASE(15)
 #undef CASE
@@ -644,7 +651,7 @@ void precond(sem_mesh m, const T* r, T* z, int pc, hipStream_t s) {
   hipStream_t sc = s;
   if (coarse) {
     if (fine) sc = fork_coarse(m, s);
-    launch_restrict<T>(m, r, sc);
+    launch_restrict<T, false>(m, const_cast<T*>(r), (const T*)nullptr, true, sc);  // r only read
     coarse_solve_tree(m, sc);
     if (sc != s) SEM_HIP(hipEventRecord(m->ev_join, sc));
   }
@@ -655,19 +662,6 @@ void precond(sem_mesh m, const T* r, T* z, int pc, hipStream_t s) {
 }
 
 // --- the steps of a PCG iteration -----------------------------------------------
-// r -= alpha A p at the interiors, with r . r and (cvec) the element parts of the
-// coarse residual over all nodes; returns the number of partial sums of r . r
-template <int N, typename T>
-int64_t launch_update_r(sem_mesh m, T* r, const T* y, bool coarse, hipStream_t s) {
-  constexpr int EPB = ax_epb<N>();
-  const int64_t grid = xcd_grid((m->T.E + EPB - 1) / EPB);
-  hipLaunchKernelGGL((update_r_kernel<N, T, EPB>), dim3((unsigned)grid), dim3(EPB * (N + 1) * (N + 1)), 0, s, r, y,
-                     (const double*)m->wk.sc, coarse ? m->cvec.p : nullptr, m->part_dst.p, m->wk.rpart, m->rec.p,
-                     (const double*)m->phi.p, m->order.p, m->T.E);
-  SEM_HIP(hipGetLastError());
-  return grid;
-}
-
 // alpha = rz / (p . A p) and r -= alpha A p; returns the number of partial sums of r . r
 template <typename T>
 int64_t pcg_update_r(sem_mesh m, T* r, const T* p, T* y, int rz, bool coarse, hipStream_t s) {
@@ -679,16 +673,7 @@ int64_t pcg_update_r(sem_mesh m, T* r, const T* p, T* y, int rz, bool coarse, hi
   hipLaunchKernelGGL((gs_r_kernel<T>), dim3((unsigned)blocks_for(m->T.base_i)), dim3(kGS), 0, s, r, Wp<T>(m),
                      shared_nodes(m), shared_coef<T>(m), p, m->wk.sc, rz, (const double*)m->wk.dpart, (int)na);
   SEM_HIP(hipGetLastError());
-  switch (m->T.N) {
-#define CASE(NN) \
-  case NN:       \
-    return launch_update_r<NN, T>(m, r, y, coarse, s);
-    CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14)
-    CASE(15)
-#undef CASE
-    default:
-      throw Error{SEM_EUNSUPPORTED, "order not compiled"};
-  }
+  return launch_restrict<T, true>(m, r, y, coarse, s);
 }
 
 // the coarse solve of the element parts in the contribution vector, its partial
@@ -1123,7 +1108,7 @@ int pcg_core(sem_mesh m, T* x, T* r, double bnorm2, double rr0, double rtol, int
     dot<T, T>(m, r, r, rz, s);
   } else {
     if (coarse) {
-      launch_restrict<T>(m, r, s);
+      launch_restrict<T, false>(m, r, (const T*)nullptr, true, s);
       pcg_start_coarse(m, fine, s);
     }
     pcg_finish<T>(m, r, x, p, fine, coarse, rz, rz, true, s);

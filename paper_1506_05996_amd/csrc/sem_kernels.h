@@ -16,6 +16,27 @@ constexpr int ax_epb() {
   return (64 / ((N + 1) * (N + 1))) > 0 ? (64 / ((N + 1) * (N + 1))) : 1;
 }
 
+// Elements per workgroup of the line-phase operator kernel and of the
+// restriction: as many as fill whole waves where one element leaves many of its
+// lanes idle ((N + 1)^2 lanes each: N = 5 uses 36 of 64 alone, 252 of 256 by
+// sevens).  Measured on 6 M local nodes, factors rebuilt, one element (two at
+// N = 4) / packed: N = 4 54.8 / 49.8 us FP64, 32.7 / 29.9 FP32; N = 5 63.8 / 47.0,
+// 39.7 / 29.8; N = 6 55.6 / 51.3, 32.6 / 30.5; N = 8 63.1 / 52.1, 37.3 / 30.2.
+// From N = 9 the lines' LDS buffers bound the elements in flight, and wider
+// workgroups only wait more at their barriers (N = 9 by threes 58.9 / 96.0, by
+// fives 71.5; N = 11 by twos 76.5 / 87.3; N = 13 by twos 67.9 / 80.2).
+template <int N>
+constexpr int line_epb() {
+  return N == 2 ? 7 : N == 3 ? 4 : N == 4 ? 5 : N == 5 ? 7 : N == 6 ? 5 : N == 8 ? 3 : 1;
+}
+
+// The sum of the corrections likewise, but for N = 4: pairs 87 us, fives 90 us
+// (FP32 fine preconditioner; it moves bytes, and its LDS stage limits it).
+template <int N>
+constexpr int sum_epb() {
+  return N == 4 ? 2 : line_epb<N>();
+}
+
 __device__ __forceinline__ void unpack_coef(int32_t code, int& ai, int& aj, int& ak) {
   ai = (int32_t)((uint32_t)code << 22) >> 22;
   aj = (int32_t)((uint32_t)code << 12) >> 22;
@@ -1477,79 +1498,20 @@ schwarz_sum_kernel(T* __restrict__ z, T* __restrict__ x, T* __restrict__ w, cons
 // owns of Phi_I(t_i) Phi_J(t_j) Phi_K(t_k) r_N  (= (I^T r) once gathered).  The
 // eight parts go, negated, to the coarse rows' own entries of the contribution
 // vector (part_dst; -1: Dirichlet vertex), where the forward sweep sums them.
-template <int N, typename T>
-__global__ void __launch_bounds__((N + 1) * (N + 1))
-restrict_kernel(const T* __restrict__ r, double* __restrict__ cvec, const int32_t* __restrict__ part_dst,
-                const int32_t* __restrict__ rec, const double* __restrict__ phi, const int32_t* __restrict__ order,
-                int64_t E) {
-  constexpr int n1 = N + 1, P = n1 * n1;
-  __shared__ double red[8][P + 1];  // padded: the eight summing lanes read eight distinct banks
-  __shared__ double sPhi[2 * n1];
-  const int tid = threadIdx.x;
-  const int i = tid % n1, j = tid / n1;
-  const int64_t pos = xcd_position(blockIdx.x, E);
-  if (pos >= E) return;  // whole workgroup
-  for (int x = tid; x < 2 * n1; x += P) sPhi[x] = phi[x];
-  const int64_t e = order[pos];
-  const int cx = node_class(i, N), cy = node_class(j, N);
-  // the three records of the lane's k-pencil, then all its residual values
-  const int4* rp = reinterpret_cast<const int4*>(rec) + e * kClasses + cx + 3 * cy;
-  const int4 r0 = rp[0], r1 = rp[9], r2 = rp[18];
-  T rv[n1];  // loaded only where the element owns the node (each global node once)
-#pragma unroll
-  for (int k = 0; k < n1; ++k) {
-    const int4 rr = k == 0 ? r0 : (k == N ? r2 : r1);
-    int ai, aj, ak;
-    unpack_coef(rr.y, ai, aj, ak);
-    rv[k] = (rr.w & kFlagOwned) ? r[rr.x + ai * i + aj * j + ak * k] : T(0);
-  }
-  __syncthreads();
-  // the lane's share of corner c: Phi_ci(t_i) Phi_cj(t_j) sum_k Phi_ck(t_k) r_k
-  double sk0 = 0.0, sk1 = 0.0;
-#pragma unroll
-  for (int k = 0; k < n1; ++k) {
-    const int4 rr = k == 0 ? r0 : (k == N ? r2 : r1);
-    if (rr.w & kFlagOwned) {
-      const double v = (double)rv[k];
-      sk0 += sPhi[k] * v;
-      sk1 += sPhi[n1 + k] * v;
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 8; ++c)
-    red[c][tid] = sPhi[(c & 1) * n1 + i] * sPhi[((c >> 1) & 1) * n1 + j] * ((c >> 2) ? sk1 : sk0);
-  __syncthreads();
-  if (tid < 8) {
-    // four interleaved partial sums, combined in a fixed order
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int x = 0;
-    for (; x + 3 < P; x += 4) {
-      s0 += red[tid][x];
-      s1 += red[tid][x + 1];
-      s2 += red[tid][x + 2];
-      s3 += red[tid][x + 3];
-    }
-    for (; x < P; ++x) s0 += red[tid][x];
-    const int32_t d = part_dst[e * 8 + tid];
-    if (d >= 0) cvec[d] = -((s0 + s1) + (s2 + s3));
-  }
-}
-
-// r -= alpha A p, second half (gs_r_kernel has done the shared nodes): the
-// interiors of each element, A p from y, and over the nodes that the element owns
-// (each global node once) the workgroup's share of r . r (rpart[block], 0 for the
-// padding blocks) and, with cvec, the element's part of the coarse restriction of
-// the updated r (as restrict_kernel).  Lets the coarse chain start right after
-// the update of r, before the patch solves.  (All in one kernel, the owner
-// summing the copies of its shared nodes, measured 69 against 40 us at 24^3,
-// N = 7: 140 VGPRs and a serial tail at edges and vertices.)
-template <int N, typename T, int EPB>
+// UPDATE: PCG's r -= alpha A p, second half (gs_r_kernel has done the shared
+// nodes): first the interiors of each element, A p from y; and over the nodes that
+// the element owns (each global node once) the workgroup's share of r . r
+// (rpart[block], 0 for the padding blocks); cvec may be NULL.  (All in one kernel,
+// the owner summing the copies of its shared nodes, measured 69 against 40 us at
+// 24^3, N = 7: 140 VGPRs and a serial tail at edges and vertices.)
+template <int N, typename T, int EPB, bool UPDATE>
 __global__ void __launch_bounds__(EPB*(N + 1) * (N + 1))
-update_r_kernel(T* __restrict__ r, const T* __restrict__ y, const double* __restrict__ sc, double* __restrict__ cvec,
+restrict_kernel(T* __restrict__ r, const T* __restrict__ y, const double* __restrict__ sc, double* __restrict__ cvec,
                 const int32_t* __restrict__ part_dst, double* __restrict__ rpart, const int32_t* __restrict__ rec,
                 const double* __restrict__ phi, const int32_t* __restrict__ order, int64_t E) {
   constexpr int n1 = N + 1, P = n1 * n1;
-  __shared__ double red[EPB][9][P + 1];  // padded rows: the summing lanes read distinct banks
+  constexpr int NV = UPDATE ? 9 : 8;  // eight parts, and r . r
+  __shared__ double red[EPB][NV][P + 1];  // padded rows: the summing lanes read distinct banks
   __shared__ double sPhi[2 * n1];
   const int tid = threadIdx.x;
   const int le = tid / P, ij = tid - le * P;
@@ -1561,7 +1523,7 @@ update_r_kernel(T* __restrict__ r, const T* __restrict__ y, const double* __rest
   const int cx = node_class(i, N), cy = node_class(j, N);
   const int4* rp = reinterpret_cast<const int4*>(rec) + e * kClasses + cx + 3 * cy;
   const int4 r0 = rp[0], r1 = rp[9], r2 = rp[18];
-  const T al = (T)sc[2];
+  const T al = UPDATE ? (T)sc[2] : T(0);
   const bool in = r1.w & kFlagInterior;  // the lane's nodes 1 <= k < N
   T rv[n1], wv[n1];
   int32_t gk[n1];  // global node ids fit in 32 bits; -1: not owned
@@ -1573,16 +1535,19 @@ update_r_kernel(T* __restrict__ r, const T* __restrict__ y, const double* __rest
     const bool own = valid && (rr.w & kFlagOwned);
     gk[k] = own ? rr.x + ai * i + aj * j + ak * k : -1;
     rv[k] = own ? r[gk[k]] : T(0);
-    wv[k] = own && in && k > 0 && k < N ? y[gk[k]] : T(0);
+    wv[k] = UPDATE && own && in && k > 0 && k < N ? y[gk[k]] : T(0);
   }
   __syncthreads();
-  // restriction as in restrict_kernel: two k-sums per lane, corner weights at the end
+  // the lane's share of corner c: Phi_ci(t_i) Phi_cj(t_j) sum_k Phi_ck(t_k) r_k
   double sk0 = 0.0, sk1 = 0.0, rsq = 0.0;
 #pragma unroll
   for (int k = 0; k < n1; ++k) {
     if (gk[k] < 0) continue;
-    const T rn = rv[k] - al * wv[k];
-    if (in && k > 0 && k < N) r[gk[k]] = rn;
+    T rn = rv[k];
+    if (UPDATE) {
+      rn -= al * wv[k];
+      if (in && k > 0 && k < N) r[gk[k]] = rn;
+    }
     const double v = (double)rn;
     rsq += v * v;
     sk0 += sPhi[k] * v;
@@ -1591,10 +1556,10 @@ update_r_kernel(T* __restrict__ r, const T* __restrict__ y, const double* __rest
 #pragma unroll
   for (int c = 0; c < 8; ++c)
     red[le][c][ij] = sPhi[(c & 1) * n1 + i] * sPhi[((c >> 1) & 1) * n1 + j] * ((c >> 2) ? sk1 : sk0);
-  red[le][8][ij] = rsq;
+  if constexpr (UPDATE) red[le][8][ij] = rsq;
   __syncthreads();
-  for (int q = tid; q < 9 * EPB; q += EPB * P) {
-    const int l = q / 9, c = q - 9 * l;
+  for (int q = tid; q < NV * EPB; q += EPB * P) {
+    const int l = q / NV, c = q - NV * l;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     int x = 0;
     for (; x + 3 < P; x += 4) {
@@ -1609,18 +1574,18 @@ update_r_kernel(T* __restrict__ r, const T* __restrict__ y, const double* __rest
       if constexpr (EPB == 1)
         rpart[blockIdx.x] = t;
       else
-        red[l][8][P] = t;
+        red[l][NV - 1][P] = t;
     } else if (cvec != nullptr && pos - le + l < E) {
       const int32_t d = part_dst[(int64_t)order[pos - le + l] * 8 + c];
       if (d >= 0) cvec[d] = -t;
     }
   }
-  if constexpr (EPB > 1) {
+  if constexpr (UPDATE && EPB > 1) {
     __syncthreads();
     if (tid == 0) {
       double t = 0.0;
 #pragma unroll
-      for (int l = 0; l < EPB; ++l) t += red[l][8][P];
+      for (int l = 0; l < EPB; ++l) t += red[l][NV - 1][P];
       rpart[blockIdx.x] = t;
     }
   }
