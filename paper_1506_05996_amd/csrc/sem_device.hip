@@ -326,7 +326,7 @@ void launch_fdm(sem_mesh m, const T* r, hipStream_t s, double* epart) {
   T* zc = ZOp<T>(m);
   T* zx = zc + m->T.E * (int64_t)m->T.n1 * m->T.n1 * m->T.n1;
   hipLaunchKernelGGL((fdm_kernel<N, T>), dim3((unsigned)fdm_grid<N>(m)), dim3(fdm_threads<N>()), 0, s, r, zc, zx,
-                     m->ip.p, m->xdest.p, Sp<T>(m), Lp<T>(m), Hp<T>(m), m->order.p, m->T.E,
+                     m->pidx.p, m->pdst.p, Sp<T>(m), Lp<T>(m), Hp<T>(m), m->order.p, m->T.E,
                      (T)m->T.kappa, (T)m->T.cmass, m->per_elem ? KEp<T>(m) : nullptr,
                      m->per_elem ? CEp<T>(m) : nullptr, epart);
   SEM_HIP(hipGetLastError());
@@ -897,8 +897,15 @@ void upload_all(sem_mesh m) {
   tq.insert(tq.end(), T.rho.begin(), T.rho.end());
   m->tq64.upload(tq.data(), tq.size());
   m->w64.alloc(T.w_size);
-  m->ip.upload(T.ip.data(), T.ip.size());
-  m->xdest.upload(T.xdest.data(), T.xdest.size());
+  if (T.N >= kPatchRecordsFrom) {
+    std::vector<int32_t> pidx, pdst;
+    build_patch_records(T, pidx, pdst);
+    m->pidx.upload(pidx.data(), pidx.size());
+    m->pdst.upload(pdst.data(), pdst.size());
+  } else {
+    m->pidx.upload(T.ip.data(), T.ip.size());
+    m->pdst.upload(T.xdest.data(), T.xdest.size());
+  }
   m->S64.upload(T.S.data(), T.S.size());
   m->lam64.upload(T.lam.data(), T.lam.size());
   m->h64.upload(T.h.data(), T.h.size());

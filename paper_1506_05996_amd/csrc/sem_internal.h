@@ -40,6 +40,10 @@ inline int32_t pack_coef(int ai, int aj, int ak) {
   return (ai & 0x3FF) | ((aj & 0x3FF) << 10) | ((ak & 0x3FF) << 20);
 }
 
+// records of the patch tables (see build_patch_records): this bit of the packed strides marks NULL
+constexpr int32_t kPatchNull = 1 << 30;
+constexpr int kPatchRecordsFrom = 5;  // orders from here use the records on the device
+
 // Coarse solve by nested dissection.  The free-vertex graph of each connected
 // component is split recursively by separators (one BFS level across the
 // longest extent); the separators and the final small parts are the nodes of
@@ -213,6 +217,7 @@ void build_reference(HostTables& T, int N);
 void build_numbering(HostTables& T, const int64_t* hex, int64_t n_hex, int64_t n_vtx);
 void build_geometry(HostTables& T, const double* vtx, const int64_t* hex);
 void build_patches(HostTables& T, const int64_t* hex);
+void build_patch_records(const HostTables& T, std::vector<int32_t>& pidx, std::vector<int32_t>& pdst);
 void build_coarse_matrices(HostTables& T, const double* vtx, const int64_t* hex);
 void build_coarse_tree(HostTables& T, int leaf_max = 0);
 void assemble_coarse_matrix(HostTables& T);

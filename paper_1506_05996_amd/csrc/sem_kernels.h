@@ -1159,17 +1159,39 @@ __device__ __forceinline__ void pencil_S(const T* __restrict__ Sp, const T (&v)[
   }
 }
 
+// The patch's node ids and consumer slots as records rather than tables with an
+// entry per slot: along each axis a patch index is below, on, inside, on or past
+// the element (patch_class 0..4), and within one of the 125 classes of (a, b, c) the
+// global id is affine (pidx [E][125]: base, packed strides, kPatchNull); the
+// outside slots' destinations are affine on each of the 26 faces, edges and corners
+// (pdst [E][26]).  Set-up derives both from the tables and checks every slot.  At
+// N = 7 a patch then reads 1.2 KB of indices instead of 6.0 KB, in the same two
+// dependent loads, and the index arithmetic of 64 slots is mostly a wave's and not
+// its lanes'.  Fine preconditioner, tables / records: N = 5 126 / 103 us on 6 M local
+// nodes FP64, N = 6 118 / 93, N = 8 91 / 83, N = 15 95 / 88.  Below N = 5 a plane
+// fills less than half a wave and the records are no smaller than the tables (N = 4
+// FP32 90 / 96, N = 3 126 / 137, N = 2 55 / 84): those orders keep the tables.
+template <int N>
+constexpr bool patch_records_on() {
+  return N >= kPatchRecordsFrom;
+}
+
+__device__ __host__ constexpr int patch_class(int a, int N) {
+  return a <= 1 ? a : (a <= N ? 2 : (a == N + 1 ? 3 : 4));
+}
+
 template <int N, typename T>
 __global__ void __launch_bounds__(fdm_threads<N>()) __attribute__((amdgpu_waves_per_eu(N <= 8 ? 8 : 4, 8)))
-fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, const int32_t* __restrict__ ip,
-           const int32_t* __restrict__ xdest, const T* __restrict__ S,
+fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, const int32_t* __restrict__ pidx,
+           const int32_t* __restrict__ pdst, const T* __restrict__ S,
            const T* __restrict__ lam, const T* __restrict__ hg, const int32_t* __restrict__ order, int64_t E,
            T kap, T cm, const T* __restrict__ ke, const T* __restrict__ ce, double* __restrict__ epart) {
+  constexpr bool REC = patch_records_on<N>();
   constexpr int m = N + 3, MM = m * m, MMM = MM * m, PPB = fdm_ppb<N>(), NT = fdm_threads<N>();
-  constexpr int NN = (N + 1) * (N + 1) * (N + 1), NX = MMM - NN, R = (PPB * MMM + NT - 1) / NT;
+  constexpr int NN = (N + 1) * (N + 1) * (N + 1), R = (PPB * MMM + NT - 1) / NT;
   __shared__ T X[PPB * MMM];
   __shared__ T sL[m];
-  __shared__ int64_t sE[PPB];  // element of each patch slot, -1 past the end
+  __shared__ int sE[PPB];  // element of each patch slot, -1 past the end
   __shared__ double sRed[NT / 64];
   const int tid = threadIdx.x;
   const int64_t pos0 = xcd_position(blockIdx.x, (E + PPB - 1) / PPB) * PPB;
@@ -1177,17 +1199,46 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
     if (epart != nullptr && tid == 0) epart[blockIdx.x] = 0.0;
     return;
   }
-  if (tid < PPB) sE[tid] = pos0 + tid < E ? (int64_t)order[pos0 + tid] : -1;
+  if (tid < PPB) sE[tid] = pos0 + tid < E ? order[pos0 + tid] : -1;
   if (tid < m) sL[tid] = lam[tid];
   __syncthreads();
-  {
+  if constexpr (REC) {
+    // lane (a, b) of a patch owns the column (a, b, 0..m-1): five records, one
+    // per class of c, then all residual loads, then the LDS stores
+    const int lq = tid / MM, ab = tid - lq * MM, a = ab % m, b = ab / m;
+    const int64_t e = tid < PPB * MM ? sE[lq] : -1;
+    if (e >= 0) {
+      const int2* rp = reinterpret_cast<const int2*>(pidx) + e * 125 + patch_class(a, N) + 5 * patch_class(b, N);
+      int2 rc[5];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) rc[q] = rp[25 * q];
+      int32_t g[5], ak[5];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        int ai, aj;
+        unpack_coef(rc[q].y, ai, aj, ak[q]);
+        g[q] = rc[q].x + ai * a + aj * b;
+      }
+      T rv[m];
+#pragma unroll
+      for (int c = 0; c < m; ++c) {
+        const int q = patch_class(c, N);
+        rv[c] = r[rc[q].y & kPatchNull ? 0 : g[q] + ak[q] * c];
+      }
+#pragma unroll
+      for (int c = 0; c < m; ++c) X[lq * MMM + c * MM + ab] = rc[patch_class(c, N)].y & kPatchNull ? T(0) : rv[c];
+    } else if (tid < PPB * MM) {
+#pragma unroll
+      for (int c = 0; c < m; ++c) X[lq * MMM + c * MM + ab] = T(0);
+    }
+  } else {
     // all index loads, then all residual loads, then the LDS stores
     int32_t gi[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       const int x = tid + q * NT, lp = min(x / MMM, PPB - 1);
       const int64_t e = x < PPB * MMM ? sE[lp] : -1;
-      gi[q] = e >= 0 ? ip[e * MMM + (x - lp * MMM)] : -1;
+      gi[q] = e >= 0 ? pidx[e * MMM + (x - lp * MMM)] : -1;
     }
     T rv[R];
 #pragma unroll
@@ -1276,14 +1327,60 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
   }
   __syncthreads();
   // Results out, driven by the destination: the element's own nodes to zc in
-  // element-local order (consecutive lanes, consecutive addresses), then the
-  // slots outside the element in their ordinal order, grouped by entity (6
-  // face planes of (N+1)^2, the lower of the other two axes fastest; 12 edge
-  // lines of N+1, edge 4 axis + side_lo + 2 side_hi; 8 corners), so that a
-  // wave's stores land in one neighbour's consumer block; xdest is read with
-  // consecutive addresses and NULL slots are dropped.
-  {
-    constexpr int n1 = N + 1, P1 = n1 * n1;
+  // element-local order, the slots outside the element in their ordinal order
+  // (grouped by entity: 6 face planes of (N+1)^2, the lower of the other two axes
+  // fastest; 12 edge lines of N+1, edge 4 axis + side_lo + 2 side_hi; 8 corners),
+  // so that a wave's stores land in one neighbour's consumer block.  NULL slots are
+  // dropped.
+  if constexpr (REC) {
+    // A wave takes 64 nodes of one plane at a time (a layer k of the own nodes, or a
+    // face of the outside slots), so that the patch, the plane and its record are
+    // uniform and a lane only adds its in-plane offset; then the edges' and corners'
+    // slots, a lane each.
+    constexpr int n1 = N + 1, P1 = n1 * n1, CH = (P1 + 63) / 64, W = NT / 64, NE = 12 * n1 + 8;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int2* prec = reinterpret_cast<const int2*>(pdst);
+    for (int t = wave; t < PPB * n1 * CH; t += W) {
+      const int lq = t / (n1 * CH), k = t / CH - lq * n1, ij = (t % CH) * 64 + lane;
+      const int eq = __builtin_amdgcn_readfirstlane(sE[lq]);
+      if (eq < 0 || (P1 % 64 != 0 && ij >= P1)) continue;
+      zc[(int64_t)eq * NN + k * P1 + ij] = X[lq * MMM + (ij % n1 + 1) + m * (ij / n1 + 1) + MM * (k + 1)];
+    }
+    for (int t = wave; t < PPB * 6 * CH; t += W) {
+      const int lq = t / (6 * CH), f = t / CH - lq * 6, uv = (t % CH) * 64 + lane;
+      const int eq = __builtin_amdgcn_readfirstlane(sE[lq]);
+      if (eq < 0) continue;
+      const int2 d = prec[(int64_t)eq * 26 + f];
+      if (d.y & kPatchNull) continue;
+      int su, sv, sw;
+      unpack_coef(d.y, su, sv, sw);
+      const int ax = f >> 1, s0 = (f & 1) ? m - 1 : 0;
+      const int lu = ax == 0 ? m : 1, lv = ax == 2 ? m : MM, l0 = s0 * (ax == 0 ? 1 : (ax == 1 ? m : MM));
+      if (P1 % 64 != 0 && uv >= P1) continue;
+      const int u = uv % n1, v = uv / n1;
+      zx[d.x + su * u + sv * v] = X[lq * MMM + l0 + lu * (u + 1) + lv * (v + 1)];
+    }
+    for (int x = tid; x < PPB * NE; x += NT) {
+      const int lq = x / NE, o = x - lq * NE;
+      const int eq = sE[lq];
+      if (eq < 0) continue;
+      const int g = o / n1, u = o < 12 * n1 ? o - g * n1 : 0, id = o < 12 * n1 ? g : o - 12 * n1;
+      const int2 d = prec[(int64_t)eq * 26 + 6 + (o < 12 * n1 ? id : 12 + id)];
+      if (d.y & kPatchNull) continue;
+      int su, sv, sw;
+      unpack_coef(d.y, su, sv, sw);
+      int off;
+      if (o < 12 * n1) {  // edge 4 axis + side_lo + 2 side_hi
+        const int ax = id >> 2, slo = (id & 1) ? m - 1 : 0, shi = (id & 2) ? m - 1 : 0;
+        off = ax == 0 ? 1 + u + m * slo + MM * shi : (ax == 1 ? slo + m * (1 + u) + MM * shi : slo + m * shi + MM * (1 + u));
+      } else {
+        off = ((id & 1) ? m - 1 : 0) + ((id & 2) ? m * (m - 1) : 0) + ((id & 4) ? MM * (m - 1) : 0);
+      }
+      zx[d.x + su * u] = X[lq * MMM + off];
+    }
+  } else {
+    // a lane per slot, with a table entry each
+    constexpr int n1 = N + 1, P1 = n1 * n1, NX = MMM - NN;
     // the lane's slots are recomputed here rather than kept live (in
     // registers) from the gather through the five passes
     int ts = tid;
@@ -1302,7 +1399,7 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
 #pragma unroll
     for (int q = 0; q < RO; ++q) {
       const int x = ts + q * NT, lq = min(x / NX, PPB - 1);
-      dq[q] = (x < PPB * NX && sE[lq] >= 0) ? xdest[sE[lq] * NX + (x - lq * NX)] : -1;
+      dq[q] = (x < PPB * NX && sE[lq] >= 0) ? pdst[(int64_t)sE[lq] * NX + (x - lq * NX)] : -1;
     }
 #pragma unroll
     for (int q = 0; q < RO; ++q) {

@@ -949,6 +949,68 @@ void build_patches(HostTables& T, const int64_t* hex) {
     }
 }
 
+// Records of the patch tables: per patch 125 classes of (a, b, c) (each axis: index
+// 0, 1, 2..N, N + 1, N + 2) with the global id base + ai a + aj b + ak c, and 26
+// entities of the outside slots (6 faces, 12 edges, 8 corners in ordinal order)
+// with the destination base + su u + sv v, (u, v) the position in the face or along
+// the edge.  [..][2] int32: base, strides (pack_coef) or kPatchNull.  Every entry of
+// ip and xdest is checked against its record.
+void build_patch_records(const HostTables& T, std::vector<int32_t>& pidx, std::vector<int32_t>& pdst) {
+  const int N = T.N, n1 = T.n1, m = T.np, P1 = n1 * n1;
+  const int64_t E = T.E, MMM = (int64_t)m * m * m, NX = T.nx;
+  pidx.assign((size_t)E * 250, 0);
+  pdst.assign((size_t)E * 52, 0);
+  const int first[5] = {0, 1, 2, N + 1, N + 2}, last[5] = {0, 1, N, N + 1, N + 2};
+  std::atomic<bool> bad{false};
+  parallel_for(E, [&](int64_t b0, int64_t b1) {
+    for (int64_t e = b0; e < b1; ++e) {
+      const int32_t* ip = &T.ip[e * MMM];
+      for (int cls = 0; cls < 125; ++cls) {
+        const int q[3] = {cls % 5, (cls / 5) % 5, cls / 25};
+        const int64_t step[3] = {1, m, (int64_t)m * m};
+        int64_t at = 0;
+        for (int d = 0; d < 3; ++d) at += first[q[d]] * step[d];
+        int64_t st[3];
+        for (int d = 0; d < 3; ++d) st[d] = last[q[d]] > first[q[d]] && ip[at] >= 0 ? (int64_t)ip[at + step[d]] - ip[at] : 0;
+        const bool null = ip[at] < 0;
+        int64_t base = ip[at];
+        for (int d = 0; d < 3; ++d) {
+          if (st[d] < -511 || st[d] > 511) bad = true;
+          base -= st[d] * first[q[d]];
+        }
+        if (base < INT32_MIN) bad = true;
+        for (int c = first[q[2]]; c <= last[q[2]]; ++c)
+          for (int b = first[q[1]]; b <= last[q[1]]; ++b)
+            for (int a = first[q[0]]; a <= last[q[0]]; ++a) {
+              const int32_t g = ip[a + (int64_t)m * (b + (int64_t)m * c)];
+              if (null ? g >= 0 : g != base + st[0] * a + st[1] * b + st[2] * c) bad = true;
+            }
+        int32_t* r = &pidx[(e * 125 + cls) * 2];
+        r[0] = null ? 0 : (int32_t)base;
+        r[1] = null ? kPatchNull : pack_coef((int)st[0], (int)st[1], (int)st[2]);
+      }
+      const int32_t* xd = &T.xdest[e * NX];
+      for (int id = 0; id < 26; ++id) {
+        const int o0 = id < 6 ? id * P1 : (id < 18 ? 6 * P1 + (id - 6) * n1 : 6 * P1 + 12 * n1 + (id - 18));
+        const int nu = id < 18 ? n1 : 1, nv = id < 6 ? n1 : 1;
+        const bool null = xd[o0] < 0;
+        const int64_t su = !null && nu > 1 ? (int64_t)xd[o0 + 1] - xd[o0] : 0;
+        const int64_t sv = !null && nv > 1 ? (int64_t)xd[o0 + n1] - xd[o0] : 0;
+        if (su < -511 || su > 511 || sv < -511 || sv > 511) bad = true;
+        for (int v = 0; v < nv; ++v)
+          for (int u = 0; u < nu; ++u) {
+            const int32_t x = xd[o0 + u + n1 * v];
+            if (null ? x >= 0 : x != xd[o0] + su * u + sv * v) bad = true;
+          }
+        int32_t* r = &pdst[(e * 26 + id) * 2];
+        r[0] = null ? 0 : xd[o0];
+        r[1] = null ? kPatchNull : pack_coef((int)su, (int)sv, 0);
+      }
+    }
+  });
+  if (bad) throw Error{SEM_EMESH, "patch table is not affine on its classes"};
+}
+
 // ---------------------------------------------------------------------------
 // coarse space: order-1 operator on the free vertices, BFS levels
 // ---------------------------------------------------------------------------
