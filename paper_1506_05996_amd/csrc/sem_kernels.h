@@ -1867,6 +1867,20 @@ coarse_fwd_kernel(double* __restrict__ X, double* __restrict__ Zv, double* __res
   }
   const CoarseTile t = tiles[blockIdx.x];
   const int lane = threadIdx.x & 63, r0 = t.row + (threadIdx.x >> 6) * RW;
+  // the row whose sum this lane ends with (wave_rows_sum): its own entries and
+  // where its result goes, loaded ahead of the products
+  const int r = r0 + lane / (64 / RW);
+  const bool mine = lane % (64 / RW) == 0 && r < t.rows;
+  double c[1] = {0.0};
+  int32_t dst = 0;
+  if (mine) {
+    const int g[1] = {t.src + r};
+    if (r >= t.s || epart != nullptr) row_entries<1, 8>(cvec, rs_off, g, c);
+    if (r >= t.s)
+      dst = cdst[t.coff + r - t.s];
+    else if (t.root)
+      dst = cvert[t.off + r];
+  }
   double acc[RW];
   coarse_tile_dots<RW, NARROW>(t, pool, r0, sv, acc, [&](int c, int end, auto& v) {
     constexpr int U = NARROW ? 1 : 4;
@@ -1878,18 +1892,14 @@ coarse_fwd_kernel(double* __restrict__ X, double* __restrict__ Zv, double* __res
     for (int u = 0; u < U; ++u) v[u] = -v[u];
   });
   const double v = wave_rows_sum<RW>(acc);
-  const int r = r0 + lane / (64 / RW);
   double en = 0.0;
-  if (lane % (64 / RW) == 0 && r < t.rows) {
-    const int g[1] = {t.src + r};
-    double c[1] = {0.0};
-    if (r >= t.s || epart != nullptr) row_entries<1, 8>(cvec, rs_off, g, c);
+  if (mine) {
     if (r < t.s) {
       X[t.off + r] = v;
-      if (t.root) Zv[cvert[t.off + r]] = v;
+      if (t.root) Zv[dst] = v;
       en = -c[0] * v;
     } else {
-      cvec[cdst[t.coff + r - t.s]] = v + c[0];
+      cvec[dst] = v + c[0];
     }
   }
   if (epart != nullptr) {
@@ -1911,6 +1921,14 @@ coarse_bwd_kernel(double* __restrict__ X, double* __restrict__ Zv, const double*
   __shared__ __attribute__((aligned(16))) double sv[NARROW ? 128 : kCoarseStage];
   const CoarseTile t = tiles[blockIdx.x];
   const int lane = threadIdx.x & 63, r0 = t.row + (threadIdx.x >> 6) * RW;
+  const int r = r0 + lane / (64 / RW);  // the row whose sum this lane ends with
+  const bool mine = lane % (64 / RW) == 0 && r < t.rows;
+  double z = 0.0;
+  int32_t dst = 0;
+  if (mine) {
+    z = X[t.off + r];
+    dst = cvert[t.off + r];
+  }
   double acc[RW];
   coarse_tile_dots<RW, NARROW>(t, pool, r0, sv, acc, [&](int c, int end, auto& v) {
     constexpr int U = NARROW ? 1 : 4;
@@ -1923,11 +1941,10 @@ coarse_bwd_kernel(double* __restrict__ X, double* __restrict__ Zv, const double*
     for (int u = 0; u < U; ++u) v[u] = c + 256 * u < end ? v[u] : 0.0;
   });
   const double v = wave_rows_sum<RW>(acc);
-  const int r = r0 + lane / (64 / RW);
-  if (lane % (64 / RW) != 0 || r >= t.rows) return;
-  const double x = X[t.off + r] - v;
-  X[t.off + r] = x;
-  Zv[cvert[t.off + r]] = x;
+  if (mine) {
+    X[t.off + r] = z - v;
+    Zv[dst] = z - v;
+  }
 }
 
 // ---------------------------------------------------------------------------
