@@ -136,14 +136,24 @@ def _ptr(a: np.ndarray):
 
 
 def _dptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_torch = None  # set by the first call that takes tensors (the host tables need none)
+
+
+def _load_torch():
+    global _torch
+    import torch
+    _torch = torch
+    return torch
 
 
 def _stream(stream=None):
     if stream is not None:
         return ctypes.c_void_p(stream)
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    torch = _torch or _load_torch()
+    return torch.cuda.current_stream().cuda_stream
 
 
 def default_solve_opts(**kw) -> SolveOpts:
@@ -238,12 +248,32 @@ class Mesh:
     # --- device calls ------------------------------------------------------
     @staticmethod
     def _dtype_code(t):
-        import torch
+        torch = _torch or _load_torch()
         if t.dtype == torch.float64:
             return SEM_F64
         if t.dtype == torch.float32:
             return SEM_F32
         raise TypeError("vectors must be float64 or float32")
+
+    def _pair(self, u, y):
+        """(pointers of u and y, dtype code) when they are what nearly every call
+        passes: distinct contiguous tensors of n_global entries of one type on the
+        handle's device.  None otherwise: the full checks then say what is wrong
+        (or accept it).  The checks are most of a small call's cost on the host."""
+        torch = _torch or _load_torch()
+        if type(u) is not torch.Tensor or type(y) is not torch.Tensor:
+            return None
+        dt = u.dtype
+        code = SEM_F64 if dt is torch.float64 else SEM_F32 if dt is torch.float32 else None
+        n = self.n_global
+        if (code is None or y.dtype is not dt or not u.is_cuda or not y.is_cuda or u.numel() != n or y.numel() != n
+                or u.get_device() != self.device or y.get_device() != self.device or not u.is_contiguous()
+                or not y.is_contiguous()):
+            return None
+        a, b = u.data_ptr(), y.data_ptr()
+        if abs(a - b) < n * (8 if code == SEM_F64 else 4):
+            return None
+        return a, b, code
 
     def _check_vecs(self, *specs):
         """specs: (tensor, name, dtype or None, length or None).  Each must be a
@@ -270,9 +300,13 @@ class Mesh:
         self._check_vecs((t, name, dtype, n))
 
     def apply_A(self, u, y=None, stream=None):
-        import torch
+        torch = _torch or _load_torch()
         if y is None:
             y = torch.empty_like(u) if isinstance(u, torch.Tensor) else None
+        fast = self._pair(u, y)
+        if fast is not None:
+            _check(_lib.sem_apply_A(self._h, fast[0], fast[1], fast[2], _stream(stream)))
+            return y
         self._check_vecs((u, "u", None, None), (y, "y", getattr(u, "dtype", None), None))
         _no_alias(u, y, "u", "y")
         _check(_lib.sem_apply_A(self._h, _dptr(u), _dptr(y), self._dtype_code(u), _stream(stream)))
@@ -303,9 +337,13 @@ class Mesh:
         return te.value, tg.value
 
     def precond(self, r, z=None, pc=PC_TWOSCALE, stream=None):
-        import torch
+        torch = _torch or _load_torch()
         if z is None:
             z = torch.empty_like(r) if isinstance(r, torch.Tensor) else None
+        fast = self._pair(r, z)
+        if fast is not None:
+            _check(_lib.sem_precond(self._h, fast[0], fast[1], fast[2], int(pc), _stream(stream)))
+            return z
         self._check_vecs((r, "r", None, None), (z, "z", getattr(r, "dtype", None), None))
         _no_alias(r, z, "r", "z")
         _check(_lib.sem_precond(self._h, _dptr(r), _dptr(z), self._dtype_code(r), int(pc), _stream(stream)))
