@@ -1082,8 +1082,8 @@ double read_scalar(sem_mesh m, int idx, hipStream_t s) {
 // interiors, then at the shared nodes.  The
 // scalar products need no assembled vector, so neither A p at the shared nodes
 // nor z is ever stored.  Against the gathers and vector updates as passes of
-// their own: PCG to 1e-10 at 24^3, N = 7 19.2 -> 17.5 ms, 56^3 218 -> 209 ms, 4^3,
-// N = 4 3.0 -> 1.8 ms, 40^3 refined 62.8 -> 59.7 ms.
+// their own: PCG to 1e-10 at 24^3, N = 7 19.2 -> 17.4 ms, 4^3,
+// N = 4 3.0 -> 1.8 ms, 40^3 refined 62.8 -> 58.7 ms.
 template <typename T>
 int pcg_core(sem_mesh m, T* x, T* r, double bnorm2, double rr0, double rtol, int max_iter, int pc, int check_every,
              hipStream_t s, int* iters, double* rel, sem_solve_stats* st) {

@@ -437,9 +437,27 @@ constexpr int dsplit_size() {
   return (n1 / 2) * (2 * (n1 / 2) + n1 % 2) + (n1 % 2) * (n1 / 2);
 }
 
+// Rows of D that the line loops hold at a time.  A row comes by scalar loads, and
+// a loop over single rows waits for each one.  In the forward loops further rows
+// cost scalar registers only; in the transposed ones all rows at once pay up to
+// N = 4 (N = 5 47 / 53 us, N = 8 53 / 60).  The pairs' tables fit the scalar
+// registers whole in FP32 up to N = 10; larger ones are taken by two rows (all
+// rows at N = 15: 65 us).  Element kernel on 6 M local nodes, factors rebuilt, one
+// row at a time / so: FP64 N = 3 46.6 / 45.1 us, N = 6 52.5 / 49.3, N = 7 46.4 / 44.3,
+// N = 11 75.8 / 72.3, N = 15 54.6 / 50.5; FP32 N = 4 30.7 / 28.9, N = 5 30.5 / 28.0,
+// N = 6 31.4 / 28.4, N = 7 28.9 / 27.0, N = 8 30.9 / 29.3, N = 15 32.5 / 30.9.  At
+// N = 9 FP64 it changes nothing, and two transposed rows take 102 instead of 57 us.
+constexpr int forward_rows(int N) { return N <= 8 ? 4 : 1; }
+constexpr int transposed_rows(int N) { return N <= 4 ? N + 1 : 1; }
+template <typename T>
+constexpr int pair_rows(int n1) {
+  return sizeof(T) == 4 && n1 <= 11 ? (n1 + 1) / 2 : 2;
+}
+
 template <int n1, typename T, typename Ld, typename St>
 __device__ __forceinline__ void line_pairs(const T* __restrict__ tb, Ld ld, St st) {
   constexpr int H = n1 / 2, OD = n1 % 2, RW = 2 * H + OD;
+  constexpr int ROWS = pair_rows<T>(n1);
   T e[H], o[H], xm = T(0);
 #pragma unroll
   for (int m = 0; m < H; ++m) {
@@ -448,7 +466,7 @@ __device__ __forceinline__ void line_pairs(const T* __restrict__ tb, Ld ld, St s
     o[m] = l - r;
   }
   if constexpr (OD) xm = ld(H);
-#pragma unroll 1
+#pragma unroll(ROWS)
   for (int q = 0; q < H; ++q) {
     const T* row = tb + q * RW;
     T E = 0, O = 0;
@@ -494,6 +512,7 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
                OpCoef<T> oc) {
   constexpr int n1 = N + 1, P = n1 * n1, NN = P * n1;
   constexpr int LS = n1 + 1, PS = n1 * LS, BS = n1 * PS;
+  constexpr int FROWS = forward_rows(N), TROWS = transposed_rows(N);
   constexpr bool PAIRS = line_pairs_on<N, T>(), ZPAIRS = zeta_pairs_on<N, T>();
   __shared__ T sX[EPB][BS];
   __shared__ T sZ[EPB][BS];
@@ -589,7 +608,7 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
       T v[n1];
 #pragma unroll
       for (int m = 0; m < n1; ++m) v[m] = X[b * PS + m * LS + a];
-#pragma unroll 1
+#pragma unroll(FROWS)
       for (int q = 0; q < n1; ++q) {
         const T* Dq = Dg + q * n1;
         T s = 0;
@@ -603,7 +622,7 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
       T v[n1];
 #pragma unroll
       for (int m = 0; m < n1; ++m) v[m] = X[b * PS + a * LS + m];
-#pragma unroll 1
+#pragma unroll(FROWS)
       for (int q = 0; q < n1; ++q) {
         const T* Dq = Dg + q * n1;
         T s = 0;
@@ -745,7 +764,7 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
     T sx[n1], sz[n1];
 #pragma unroll
     for (int q = 0; q < n1; ++q) sx[q] = sz[q] = T(0);
-#pragma unroll 1
+#pragma unroll(TROWS)
     for (int m = 0; m < n1; ++m) {
       const T* Dm = Dg + m * n1;
       const T vx = X[b * PS + a * LS + m], vz = Z[b * PS + m * LS + a];
