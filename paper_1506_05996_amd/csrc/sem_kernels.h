@@ -414,22 +414,28 @@ ax_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, const T
 // entry m of the line, st(q, v) writes output q; every read comes first, so
 // the output may overwrite the line.
 // Whether the line-phase operator kernel contracts its lines by output pairs:
-// everywhere but the FP64 kernels up to N = 9, which run at the 128-VGPR limit
-// of 4 waves per SIMD and measure faster with the row-by-row form (at 56^3,
-// N = 7: 0.628-0.636 ms against 0.635-0.651 ms; at N = 15 the pairs take
-// FP64 from 0.330 to 0.306 ms and FP32 from 0.171 to 0.151 ms).
+// FP32 everywhere (N = 15 0.171 -> 0.151 ms at 20^3), FP64 at N = 4 and 5, whose
+// tables fit the scalar registers, and from N = 9, with the zeta pairs below.  An
+// application by rows / by pairs, FP64: N = 4 at 36^3 53.3 / 50.8 us, N = 5 at 28^3
+// 43.7 / 41.3, N = 9 at 16^3 46.3 / 44.8; N = 8 at 18^3 42.0 / 42.5, and at N = 3 and 6
+// the element kernel alone is no faster.  At N = 7 (with the zeta pairs) 697 us at
+// 56^3 against 693 by single rows, and a heat step on 10 x 10 x 125 elements 10.70
+// against 10.44 ms.
 template <int N, typename T>
 constexpr bool line_pairs_on() {
-  return !(N <= 9 && sizeof(T) == 8);
+  return sizeof(T) == 4 || N == 4 || N == 5 || N >= 9;
 }
 
 // Whether the pencil's nodes k and N-k are processed together (the zeta
-// derivative and the zeta part of D^T C by output pairs as well): from N = 10,
-// where the kernel has registers to spare (N = 15: 0.303-0.308 -> 0.288-0.289 ms
-// FP64, 0.150-0.154 -> 0.139 ms FP32); at N = 7 FP32 it measured 2-3% slower.
+// derivative and the zeta part of D^T C by output pairs as well): from N = 10
+// (N = 15 at 20^3: 0.303-0.308 -> 0.288-0.289 ms FP64, 0.150-0.154 -> 0.139 ms FP32),
+// and at N = 7 and 9, whose pencils have no middle node: without / with on 6 M
+// local nodes N = 7 27.0 / 26.4 us FP32; N = 9 57.4 / 55.6 FP64, 35.1 / 33.0 FP32.
+// With a middle node FP64 runs out of registers (N = 6 50 / 58, N = 8 51 / 77), and
+// shorter pencils gain nothing.
 template <int N, typename T>
 constexpr bool zeta_pairs_on() {
-  return line_pairs_on<N, T>() && N >= 10;
+  return line_pairs_on<N, T>() && (N >= 10 || N == 7 || N == 9);
 }
 
 template <int n1>
@@ -438,20 +444,19 @@ constexpr int dsplit_size() {
 }
 
 // Rows of D that the line loops hold at a time.  A row comes by scalar loads, and
-// a loop over single rows waits for each one.  In the forward loops further rows
-// cost scalar registers only; in the transposed ones all rows at once pay up to
-// N = 4 (N = 5 47 / 53 us, N = 8 53 / 60).  The pairs' tables fit the scalar
-// registers whole in FP32 up to N = 10; larger ones are taken by two rows (all
-// rows at N = 15: 65 us).  Element kernel on 6 M local nodes, factors rebuilt, one
-// row at a time / so: FP64 N = 3 46.6 / 45.1 us, N = 6 52.5 / 49.3, N = 7 46.4 / 44.3,
-// N = 11 75.8 / 72.3, N = 15 54.6 / 50.5; FP32 N = 4 30.7 / 28.9, N = 5 30.5 / 28.0,
-// N = 6 31.4 / 28.4, N = 7 28.9 / 27.0, N = 8 30.9 / 29.3, N = 15 32.5 / 30.9.  At
-// N = 9 FP64 it changes nothing, and two transposed rows take 102 instead of 57 us.
-constexpr int forward_rows(int N) { return N <= 8 ? 4 : 1; }
-constexpr int transposed_rows(int N) { return N <= 4 ? N + 1 : 1; }
+// a loop over single rows waits for each one.  The pairs' tables fit the scalar
+// registers whole in FP32 up to N = 10 and in FP64 up to N = 5; larger ones are
+// taken by two rows (all rows at N = 15: 65 us).  Row by row (the other orders in FP64) the
+// forward loops hold four rows, which costs scalar registers only, and the
+// transposed ones all of them where a line is short.  Element kernel on 6 M local
+// nodes, factors rebuilt, one row at a time / so: FP64 N = 3 46.6 / 45.1 us, N = 6
+// 52.5 / 49.3, N = 7 46.4 / 44.6, N = 11 75.8 / 72.3, N = 15 54.6 / 50.5; FP32 N = 4 30.7 / 28.9, N = 5
+// 30.5 / 28.0, N = 6 31.4 / 28.4, N = 7 28.9 / 27.0, N = 8 30.9 / 29.3, N = 15 32.5 / 30.9.
+constexpr int kForwardRows = 4;
+constexpr int transposed_rows(int N) { return N <= 3 ? N + 1 : 1; }
 template <typename T>
 constexpr int pair_rows(int n1) {
-  return sizeof(T) == 4 && n1 <= 11 ? (n1 + 1) / 2 : 2;
+  return n1 <= (sizeof(T) == 4 ? 11 : 6) ? (n1 + 1) / 2 : 2;
 }
 
 template <int n1, typename T, typename Ld, typename St>
@@ -466,7 +471,7 @@ __device__ __forceinline__ void line_pairs(const T* __restrict__ tb, Ld ld, St s
     o[m] = l - r;
   }
   if constexpr (OD) xm = ld(H);
-#pragma unroll(ROWS)
+#pragma unroll ROWS
   for (int q = 0; q < H; ++q) {
     const T* row = tb + q * RW;
     T E = 0, O = 0;
@@ -512,7 +517,7 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
                OpCoef<T> oc) {
   constexpr int n1 = N + 1, P = n1 * n1, NN = P * n1;
   constexpr int LS = n1 + 1, PS = n1 * LS, BS = n1 * PS;
-  constexpr int FROWS = forward_rows(N), TROWS = transposed_rows(N);
+  constexpr int TROWS = transposed_rows(N);
   constexpr bool PAIRS = line_pairs_on<N, T>(), ZPAIRS = zeta_pairs_on<N, T>();
   __shared__ T sX[EPB][BS];
   __shared__ T sZ[EPB][BS];
@@ -608,7 +613,7 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
       T v[n1];
 #pragma unroll
       for (int m = 0; m < n1; ++m) v[m] = X[b * PS + m * LS + a];
-#pragma unroll(FROWS)
+#pragma unroll kForwardRows
       for (int q = 0; q < n1; ++q) {
         const T* Dq = Dg + q * n1;
         T s = 0;
@@ -622,7 +627,7 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
       T v[n1];
 #pragma unroll
       for (int m = 0; m < n1; ++m) v[m] = X[b * PS + a * LS + m];
-#pragma unroll(FROWS)
+#pragma unroll kForwardRows
       for (int q = 0; q < n1; ++q) {
         const T* Dq = Dg + q * n1;
         T s = 0;
@@ -764,7 +769,7 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
     T sx[n1], sz[n1];
 #pragma unroll
     for (int q = 0; q < n1; ++q) sx[q] = sz[q] = T(0);
-#pragma unroll(TROWS)
+#pragma unroll TROWS
     for (int m = 0; m < n1; ++m) {
       const T* Dm = Dg + m * n1;
       const T vx = X[b * PS + a * LS + m], vz = Z[b * PS + m * LS + a];
