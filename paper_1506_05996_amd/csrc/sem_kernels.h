@@ -1031,7 +1031,7 @@ template <typename T>
 __global__ void __launch_bounds__(256)
 gs_px_kernel(T* __restrict__ x, T* __restrict__ p, const T* __restrict__ w, SharedNodes sn,
              const double* __restrict__ sc, int start) {
-  if (sc[6] != 0.0) return;  // whole grid
+  if (sc[6] != 0.0 || !isfinite(sc[3])) return;  // whole grid: schwarz_sum_kernel did nothing either
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= sn.base_i) return;
   const T al = (T)sc[2], beta = (T)sc[3];
@@ -1049,6 +1049,12 @@ gs_px_kernel(T* __restrict__ x, T* __restrict__ p, const T* __restrict__ w, Shar
     x[g] = xg + al * pg;
     p[g] = z + beta * pg;
   }
+}
+
+// a step of PCG breaks down on p^T A p <= 0 or an alpha that is not finite, or on
+// the beta before it (0 at the first step), which made no new p
+__device__ __forceinline__ bool step_breaks(double pAp, double alpha, const double* __restrict__ sc) {
+  return !(pAp > 0.0) || !isfinite(alpha) || !isfinite(sc[3]);
 }
 
 // sum of n partial sums by every workgroup of a consuming kernel (one wave or
@@ -1075,7 +1081,8 @@ __device__ __forceinline__ double all_partials(const double* __restrict__ part, 
 // PCG's r -= alpha A p at the shared nodes: A p gathered from the work array
 // (with the coefficients, as gs_kernel; u = p), not stored.  alpha comes from
 // sc[2], or, with na > 0, from the na partial sums of p . A p (every workgroup
-// sums them; block 0 also stores the scalars).
+// sums them; block 0 also stores the scalars, and the breakdown flag, which this
+// kernel does not read).
 template <typename T>
 __global__ void __launch_bounds__(256)
 gs_r_kernel(T* __restrict__ r, const T* __restrict__ w, SharedNodes sn, OpCoef<T> oc, const T* __restrict__ u,
@@ -1087,7 +1094,7 @@ gs_r_kernel(T* __restrict__ r, const T* __restrict__ w, SharedNodes sn, OpCoef<T
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       sc[1] = t;
       sc[2] = a;
-      if (!(t > 0.0) || !isfinite(a)) sc[6] = 1.0;
+      if (step_breaks(t, a, sc)) sc[6] = 1.0;
     }
     al = (T)a;
   } else {
@@ -1468,6 +1475,10 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
 //              the patch solves' and the coarse solve's energies.  beta comes
 //              from sc[3], or, with nb > 0, from the nb partial sums themselves
 //              (every workgroup sums them; block 0 also stores the scalars).
+//              The breakdown flag is read here, so it is not raised here: waves of
+//              one workgroup would see it at different times and part before the
+//              barriers.  A beta that is not finite stays in sc[3], where gs_px_kernel
+//              sees it, and the next step's alpha raises the flag.
 // ---------------------------------------------------------------------------
 enum : int { kSumZ = 0, kSumStart = 1, kSumPx = 2 };
 
@@ -1497,7 +1508,6 @@ schwarz_sum_kernel(T* __restrict__ z, T* __restrict__ x, T* __restrict__ w, cons
       if (blockIdx.x == 0 && tid == 0) {
         sc[3] = bd;
         sc[rz_out] = t;
-        if (!isfinite(bd)) sc[6] = 1.0;
       }
       if (!isfinite(bd)) return;  // every workgroup alike
       beta = (T)bd;
@@ -2242,7 +2252,7 @@ __device__ __forceinline__ void pcg_scalar(double s, double* sc, int dst, int mo
                                            double* host) {
   if (mode == 1) {
     const double a = sc[rz_in] / s;
-    if (!(s > 0.0) || !isfinite(a)) sc[6] = 1.0;
+    if (step_breaks(s, a, sc)) sc[6] = 1.0;
     sc[1] = s;
     sc[2] = a;
   } else if (mode == 2) {
