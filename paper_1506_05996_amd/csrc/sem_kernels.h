@@ -76,13 +76,13 @@ __device__ __forceinline__ T op_value(const OpCoef<T>& oc, T stiff, int64_t g, T
 // so that the scalar product needs no assembled vector (u is 0 on the Dirichlet
 // set, where the operator's result is masked).  With constant coefficients the
 // mass term is added at assembly; the element that owns the node counts it.
+// kappa multiplies v ahead of u: u is about 1 / kappa times v's final size, and their
+// product alone would leave the FP64 range where the energy does not.
 template <typename T>
 __device__ __forceinline__ double local_energy(const OpCoef<T>& oc, T v, T u, int64_t g, bool owned) {
-  double d = (double)u * (double)v;
-  if (oc.scaled) {
-    d *= (double)oc.kap;
-    if (oc.cm != T(0) && owned) d += (double)oc.cm * (double)oc.mN[g] * (double)u * (double)u;
-  }
+  if (!oc.scaled) return (double)u * (double)v;
+  double d = (double)u * ((double)oc.kap * (double)v);
+  if (oc.cm != T(0) && owned) d += (double)oc.cm * (double)oc.mN[g] * (double)u * (double)u;
   return d;
 }
 
