@@ -366,7 +366,11 @@ ax_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, const T
     }
   }
   // interior results straight to y, shared ones to the work array; with dpart,
-  // this workgroup's share of u^T A u
+  // this workgroup's share of u^T A u, node by node: a loop of its own over the
+  // kept values takes 6 to 66 more VGPRs here (N = 7 FP64 spills 29), which costs
+  // waves whether or not dpart is there (factors rebuilt, loop / node by node: N = 2
+  // at 48^3 34.1 / 31.6 us FP64, N = 7 at 24^3 66.0 / 60.5 FP64, N = 15 at 10^3
+  // 52.0 / 44.9 FP32)
   double dacc = 0.0;
   if (valid) {
     const bool masked_interior = rec[(e * kClasses + kInteriorClass) * kRecInts + 3] & kFlagMaskedInterior;
@@ -377,22 +381,13 @@ ax_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, const T
       int ai, aj, ak;
       unpack_coef(r.y, ai, aj, ak);
       const int off = ai * i + aj * j + ak * k;
-      const T uk = ((r.w & kFlagInterior) || oc.ke != nullptr) ? sU[le][k * P + ij] : T(0);
+      const T uk = ((r.w & kFlagInterior) || oc.ke != nullptr || dpart != nullptr) ? sU[le][k * P + ij] : T(0);
       const T v = elem_value(oc, ec, e, NN, k * P + ij, rw[k], uk);
       if (r.w & kFlagInterior)
         y[r.x + off] = (masked_interior && dir[r.x + off]) ? T(0) : op_value(oc, v, r.x + off, uk);
       else
         w[r.z + off] = v;
-      rw[k] = v;
-    }
-    if (dpart != nullptr) {
-#pragma unroll
-      for (int k = 0; k < n1; ++k) {
-        const int4 r = k == 0 ? r0 : (k == N ? r2 : r1);
-        int ai, aj, ak;
-        unpack_coef(r.y, ai, aj, ak);
-        dacc += local_energy(oc, rw[k], sU[le][k * P + ij], r.x + ai * i + aj * j + ak * k, r.w & kFlagOwned);
-      }
+      if (dpart != nullptr) dacc += local_energy(oc, v, uk, r.x + off, r.w & kFlagOwned);
     }
   }
   if (dpart != nullptr) {
