@@ -195,7 +195,7 @@ int64_t launch_ax_tile(sem_mesh m, const T* u, T* y, double* dpart, hipStream_t 
 
 template <int N, typename T, bool GEO, bool KN = false>
 int64_t launch_ax_line(sem_mesh m, const T* u, T* y, double* dpart, hipStream_t s) {
-  constexpr int EPB = line_epb<N>();
+  constexpr int EPB = line_epb<N, GEO>();
   const HostTables& T_ = m->T;
   const int64_t grid = xcd_grid((T_.E + EPB - 1) / EPB);
   hipLaunchKernelGGL((ax_line_kernel<N, T, EPB, GEO, KN>), dim3((unsigned)grid), dim3(EPB * (N + 1) * (N + 1)), 0, s,

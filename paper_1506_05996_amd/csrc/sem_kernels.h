@@ -24,10 +24,11 @@ constexpr int ax_epb() {
 // 39.7 / 29.8; N = 6 55.6 / 51.3, 32.6 / 30.5; N = 8 63.1 / 52.1, 37.3 / 30.2.
 // From N = 9 the lines' LDS buffers bound the elements in flight, and wider
 // workgroups only wait more at their barriers (N = 9 by threes 58.9 / 96.0, by
-// fives 71.5; N = 11 by twos 76.5 / 87.3; N = 13 by twos 67.9 / 80.2).
-template <int N>
+// fives 71.5; N = 11 by twos 76.5 / 87.3; N = 13 by twos 67.9 / 80.2).  With stored
+// factors (GEO false) N = 6 stays alone: 42.9 / 46.8 us FP64 at 22^3, 26.8 / 27.8 FP32.
+template <int N, bool GEO = true>
 constexpr int line_epb() {
-  return N == 2 ? 7 : N == 3 ? 4 : N == 4 ? 5 : N == 5 ? 7 : N == 6 ? 5 : N == 8 ? 3 : 1;
+  return N == 2 ? 7 : N == 3 ? 4 : N == 4 ? 5 : N == 5 ? 7 : N == 6 ? (GEO ? 5 : 1) : N == 8 ? 3 : 1;
 }
 
 // The sum of the corrections likewise, but for N = 4: pairs 87 us, fives 90 us
@@ -427,10 +428,11 @@ constexpr bool line_pairs_on() {
 // and at N = 7 and 9, whose pencils have no middle node: without / with on 6 M
 // local nodes N = 7 27.0 / 26.4 us FP32; N = 9 57.4 / 55.6 FP64, 35.1 / 33.0 FP32.
 // With a middle node FP64 runs out of registers (N = 6 50 / 58, N = 8 51 / 77), and
-// shorter pencils gain nothing.
-template <int N, typename T>
+// shorter pencils gain nothing.  N = 7 FP32 with stored factors and an element's
+// coefficients is slower with them (see pair_rows).
+template <int N, typename T, bool GEO>
 constexpr bool zeta_pairs_on() {
-  return line_pairs_on<N, T>() && (N >= 10 || N == 7 || N == 9);
+  return line_pairs_on<N, T>() && (N >= 10 || (N == 7 && GEO) || N == 9);
 }
 
 template <int n1>
@@ -447,17 +449,20 @@ constexpr int dsplit_size() {
 // nodes, factors rebuilt, one row at a time / so: FP64 N = 3 46.6 / 45.1 us, N = 6
 // 52.5 / 49.3, N = 7 46.4 / 44.6, N = 11 75.8 / 72.3, N = 15 54.6 / 50.5; FP32 N = 4 30.7 / 28.9, N = 5
 // 30.5 / 28.0, N = 6 31.4 / 28.4, N = 7 28.9 / 27.0, N = 8 30.9 / 29.3, N = 15 32.5 / 30.9.
+// With stored factors N = 7 FP32 keeps single rows and no zeta pairs: an element's
+// coefficients on 20^3 elements 30.4 us with both, 31.7 with the rows alone, 28.1 so.
 constexpr int kForwardRows = 4;
 constexpr int transposed_rows(int N) { return N <= 3 ? N + 1 : 1; }
-template <typename T>
+template <typename T, bool GEO>
 constexpr int pair_rows(int n1) {
+  if (!GEO && n1 == 8) return 1;
   return n1 <= (sizeof(T) == 4 ? 11 : 6) ? (n1 + 1) / 2 : 2;
 }
 
-template <int n1, typename T, typename Ld, typename St>
+template <int n1, typename T, bool GEO, typename Ld, typename St>
 __device__ __forceinline__ void line_pairs(const T* __restrict__ tb, Ld ld, St st) {
   constexpr int H = n1 / 2, OD = n1 % 2, RW = 2 * H + OD;
-  constexpr int ROWS = pair_rows<T>(n1);
+  constexpr int ROWS = pair_rows<T, GEO>(n1);
   T e[H], o[H], xm = T(0);
 #pragma unroll
   for (int m = 0; m < H; ++m) {
@@ -513,7 +518,7 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
   constexpr int n1 = N + 1, P = n1 * n1, NN = P * n1;
   constexpr int LS = n1 + 1, PS = n1 * LS, BS = n1 * PS;
   constexpr int TROWS = transposed_rows(N);
-  constexpr bool PAIRS = line_pairs_on<N, T>(), ZPAIRS = zeta_pairs_on<N, T>();
+  constexpr bool PAIRS = line_pairs_on<N, T>(), ZPAIRS = zeta_pairs_on<N, T, GEO>();
   __shared__ T sX[EPB][BS];
   __shared__ T sZ[EPB][BS];
   __shared__ double sRed[EPB * P];
@@ -594,11 +599,11 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
   const T* DTsp = Dsp + dsplit_size<n1>();  // D^T
   if constexpr (PAIRS) {
     // eta lines: lane (i = a, k = b)
-    line_pairs<n1, T>(Dsp, [&](int m) { return X[b * PS + m * LS + a]; },
+    line_pairs<n1, T, GEO>(Dsp, [&](int m) { return X[b * PS + m * LS + a]; },
                       [&](int q, T v) { Z[b * PS + q * LS + a] = v; });
     __syncthreads();
     // xi lines: lane (j = a, k = b), in place
-    line_pairs<n1, T>(Dsp, [&](int m) { return X[b * PS + a * LS + m]; },
+    line_pairs<n1, T, GEO>(Dsp, [&](int m) { return X[b * PS + a * LS + m]; },
                       [&](int q, T v) { X[b * PS + a * LS + q] = v; });
     __syncthreads();
   } else {
@@ -754,9 +759,9 @@ ax_line_kernel(const T* __restrict__ u, T* __restrict__ y, T* __restrict__ w, co
   __syncthreads();
   // transposed xi lines (lane (j = a, k = b)) and eta lines (lane (i = a, k = b)), in place
   if constexpr (PAIRS) {
-    line_pairs<n1, T>(DTsp, [&](int m) { return X[b * PS + a * LS + m]; },
+    line_pairs<n1, T, GEO>(DTsp, [&](int m) { return X[b * PS + a * LS + m]; },
                       [&](int q, T v) { X[b * PS + a * LS + q] = v; });
-    line_pairs<n1, T>(DTsp, [&](int m) { return Z[b * PS + m * LS + a]; },
+    line_pairs<n1, T, GEO>(DTsp, [&](int m) { return Z[b * PS + m * LS + a]; },
                       [&](int q, T v) { Z[b * PS + q * LS + a] = v; });
   } else {
     // loop over the input index m: row m of D in scalar registers scales line
