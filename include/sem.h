@@ -195,7 +195,7 @@ int sem_coarse_solve(sem_mesh m, const double* R_dev, double* Z_dev, void* strea
  * of those values.  b = 0 gives x = 0 and 0 iterations; with use_x0, a start
  * whose residual already meets the tolerance returns after 0 iterations.
  * After SEM_EBREAKDOWN x holds the last iterate with finite scalars.
- * Work vectors (4 of n_global FP64, and 4 FP32 for the refined form) are
+ * Work vectors (3 of n_global FP64, and 4 FP32 for the refined form) are
  * allocated by the first solve that needs them and kept by the handle.
  */
 int sem_pcg_solve(sem_mesh m, const double* b_dev, double* x_dev, const sem_solve_opts* o,
@@ -208,9 +208,10 @@ int sem_pcg_solve(sem_mesh m, const double* b_dev, double* x_dev, const sem_solv
  * sem_pcg_solve; the work vectors, partial sums and scalars of the solve live
  * in one static device array of the library (128 MiB per device, held until
  * the process ends) instead of the handle's lazily allocated buffers, and the
- * call allocates nothing.  Needed: 40 bytes per global node (FP64), 60 with
- * SEM_SOLVE_FP32_REFINED, plus about 8 bytes per element (about 3.3 M and 2.2 M global nodes at
- * most); a larger mesh gives SEM_EINVAL and a message naming both sizes,
+ * call allocates nothing.  Accepted: meshes for which 40 bytes per global node
+ * (FP64; 60 with SEM_SOLVE_FP32_REFINED) plus 8 bytes per element and 1/32 byte
+ * per shared node fit the array (about 3.3 M and 2.2 M global nodes at most; a
+ * solve uses less of it); a larger mesh gives SEM_EINVAL and a message naming both sizes,
  * before any device work.  Everything the solve reads is built at set-up (for the
  * AMG coarse solver its graph and the side stream); if a later call on the handle dropped
  * one of them, the call fails with SEM_EINVAL instead of rebuilding it.  All

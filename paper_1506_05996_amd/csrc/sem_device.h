@@ -128,14 +128,14 @@ struct sem_mesh_s {
   hipGraphExec_t amg_graph = nullptr;
   // PCG work: the handle's own buffers (allocated by the first solve that
   // needs them) ...
-  DBuf<double> v64[5];
-  DBuf<float> v32[5];
+  DBuf<double> v64[3];
+  DBuf<float> v32[4];
   DBuf<double> part, sc, parts;
   // ... and the pointers one solve works in: the buffers above, or views into
   // the library's static scratch array (sem_pcg_solve_noalloc)
   struct SolveWork {
-    double* v64[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-    float* v32[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+    double* v64[3] = {nullptr, nullptr, nullptr};           // r, p, A p
+    float* v32[4] = {nullptr, nullptr, nullptr, nullptr};  // r, p, A p, and the refined form's correction
     double* part = nullptr;   // kRedBlocks partial sums
     double* sc = nullptr;     // 16 device scalars of Algorithm 1
     // per-workgroup partial sums: p . A p, r . r, and r . z (patch solves, then coarse solve)

@@ -966,15 +966,17 @@ void set_parts(sem_mesh m, double* base) {
 }
 
 // the handle's own solve buffers (allocated on first need) as the work of the
-// next solve (vector 2 of each set is not used)
+// next solve
 void ensure_work(sem_mesh m, bool need32) {
   const int64_t n = m->T.n_global;
   const size_t np = part_counts(m).total();
   if (m->parts.n < np) m->parts.alloc(np);
-  for (int q = 0; q < 5; ++q) {
-    if (q != 2 && m->v64[q].n != (size_t)n) m->v64[q].alloc(n);
-    if (q != 2 && need32 && m->v32[q].n != (size_t)n) m->v32[q].alloc(n);
+  for (int q = 0; q < 3; ++q) {
+    if (m->v64[q].n != (size_t)n) m->v64[q].alloc(n);
     m->wk.v64[q] = m->v64[q].p;
+  }
+  for (int q = 0; q < 4; ++q) {
+    if (need32 && m->v32[q].n != (size_t)n) m->v32[q].alloc(n);
     m->wk.v32[q] = need32 ? m->v32[q].p : nullptr;
   }
   m->wk.part = m->part.p;
@@ -983,8 +985,8 @@ void ensure_work(sem_mesh m, bool need32) {
 }
 
 // --- static scratch of sem_pcg_solve_noalloc ------------------------------
-// The work of one solve (Algorithm 1's scalars, partial sums and the five FP64
-// vectors, plus five FP32 vectors for the refined form) as views into one
+// The work of one solve (Algorithm 1's scalars, partial sums and three FP64
+// vectors, plus four FP32 vectors for the refined form) as views into one
 // file-scope device array, for callers that cannot allocate device memory.
 // Every device holds its own copy of the array, at its own address, resolved
 // once per device at set-up (create_mesh) with that device current; host code
@@ -1012,43 +1014,45 @@ double* scratch_of(int device) {
 
 // byte offsets of one solve's work inside the scratch array (256-aligned parts)
 struct ScratchLayout {
-  size_t sc, part, v64, v32, total;
+  size_t sc, part, parts, v64, v32, s64, s32;  // s64, s32: bytes from one vector to the next
+  size_t total;
 };
 
 ScratchLayout scratch_layout(sem_mesh m, bool need32) {
   auto up = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
   const size_t n = (size_t)m->T.n_global;
   ScratchLayout L{};
+  L.s64 = up(n * sizeof(double));
+  L.s32 = up(n * sizeof(float));
   size_t o = 0;
-  L.sc = o;
-  o += up(16 * sizeof(double));
-  L.part = o;
-  o += up(kRedBlocks * sizeof(double));
-  o += up((size_t)(xcd_grid(m->T.E) + blocks_for(m->T.base_i)) * sizeof(double));  // not used
-  L.v64 = o;
-  o += 5 * up(n * sizeof(double));
-  L.v32 = o;
-  if (need32) o += 5 * up(n * sizeof(float));
-  L.total = o;
+  auto take = [&](size_t bytes) {
+    const size_t at = o;
+    o += up(bytes);
+    return at;
+  };
+  L.sc = take(16 * sizeof(double));
+  L.part = take(kRedBlocks * sizeof(double));
+  const size_t vectors = o;
+  L.parts = take(part_counts(m).total() * sizeof(double));
+  L.v64 = take(3 * L.s64);
+  L.v32 = take(need32 ? 4 * L.s32 : 0);
+  // which meshes the call takes is part of its interface (40 bytes per global
+  // node, 60 in the refined form): what a solve no longer needs stays counted
+  const size_t stated = vectors + up((size_t)(xcd_grid(m->T.E) + blocks_for(m->T.base_i)) * sizeof(double)) +
+                        5 * L.s64 + (need32 ? 5 * L.s32 : 0);
+  L.total = std::max(o, stated);
   return L;
 }
 
 // the next solve's work as views into the scratch array at `base`
 void scratch_work(sem_mesh m, bool need32, double* base) {
   const ScratchLayout L = scratch_layout(m, need32);
-  const size_t n = (size_t)m->T.n_global;
   char* c = reinterpret_cast<char*>(base);
-  const size_t s64 = (n * sizeof(double) + 255) / 256 * 256, s32 = (n * sizeof(float) + 255) / 256 * 256;
-  for (int q = 0; q < 5; ++q) {
-    m->wk.v64[q] = reinterpret_cast<double*>(c + L.v64 + q * s64);
-    m->wk.v32[q] = need32 ? reinterpret_cast<float*>(c + L.v32 + q * s32) : nullptr;
-  }
+  for (int q = 0; q < 3; ++q) m->wk.v64[q] = reinterpret_cast<double*>(c + L.v64 + q * L.s64);
+  for (int q = 0; q < 4; ++q) m->wk.v32[q] = need32 ? reinterpret_cast<float*>(c + L.v32 + q * L.s32) : nullptr;
   m->wk.part = reinterpret_cast<double*>(c + L.part);
   m->wk.sc = reinterpret_cast<double*>(c + L.sc);
-  // vector 2 is not used by the solve: its place takes the partial sums (at most
-  // about three per element, against at least eight nodes)
-  if (part_counts(m).total() > n) throw Error{SEM_EINVAL, "static scratch: partial sums do not fit"};
-  set_parts(m, m->wk.v64[2]);
+  set_parts(m, reinterpret_cast<double*>(c + L.parts));
 }
 
 template <typename TA, typename TB>
@@ -1090,11 +1094,11 @@ int pcg_core(sem_mesh m, T* x, T* r, double bnorm2, double rr0, double rtol, int
   T* p;
   T* w;
   if constexpr (std::is_same<T, double>::value) {
-    p = m->wk.v64[3];
-    w = m->wk.v64[4];
+    p = m->wk.v64[1];
+    w = m->wk.v64[2];
   } else {
-    p = m->wk.v32[3];
-    w = m->wk.v32[4];
+    p = m->wk.v32[1];
+    w = m->wk.v32[2];
   }
   double* sc = m->wk.sc;
   const int64_t n = m->T.n_global;
@@ -1374,8 +1378,8 @@ int solve_impl(sem_mesh m, const double* b, double* x, const sem_solve_opts* o, 
   const int nb = (int)std::min<int64_t>(kRedBlocks, blocks_for(n, kRedThreads));
   const int check = std::max(1, o->check_every);
   if (st) st->history_len = 0;
-  double* r64 = m->wk.v64[1];
-  double* Ax = m->wk.v64[4];
+  double* r64 = m->wk.v64[0];
+  double* Ax = m->wk.v64[2];
   // r = mask(b - A x) with ||r||^2 into scalar slot `slot` (Ax = NULL: r = mask(b))
   auto residual = [&](const double* ax, int slot) {
     hipLaunchKernelGGL(residual_kernel, dim3(nb), dim3(kRedThreads), 0, s, r64, b, ax, (const uint8_t*)m->dir.p,
@@ -1427,8 +1431,8 @@ int solve_impl(sem_mesh m, const double* b, double* x, const sem_solve_opts* o, 
     }
   } else {
     // outer FP64 refinement around FP32 inner PCG solves
-    float* d32 = m->wk.v32[0];
-    float* r32 = m->wk.v32[1];
+    float* r32 = m->wk.v32[0];
+    float* d32 = m->wk.v32[3];
     if (!o->use_x0) hipLaunchKernelGGL((fill_kernel<double>), dim3(gb), dim3(kGS), 0, s, x, 0.0, n);
     status = SEM_ENOCONV;
     const double tol2 = o->rtol * o->rtol * bnorm2;
