@@ -89,24 +89,39 @@ def algorithmic_flops_ax(n_local, N, geometry_on_the_fly):
     return n_local * (12 * (N + 1) + 18 + (104 if geometry_on_the_fly else 0))
 
 
+PATCH_RECORDS_FROM = 5  # orders from here read the patch records, lower ones the patch tables (kPatchRecordsFrom)
+
+
+def operator_bytes(E, N, n_local, n_global, s):
+    """(element kernel, shared-node gather) bytes of one operator application with the factors
+    rebuilt from the vertices, each array counted once: input, entity records (27 of 16 B) and 24
+    vertex coordinates per element, interior results, shared results to the work array; then the work
+    array and the shared nodes."""
+    interior = E * (N - 1) ** 3
+    shared = n_local - interior
+    return (s * n_global + (432 + 24 * s) * E + s * interior + s * shared,
+            s * shared + s * (n_global - interior))
+
+
 def pcg_iteration_bytes(E, N, n_local, n_global, coarse_entries, s):
-    """Algorithmic HBM bytes of one PCG iteration as the path runs it, with the
-    fine-level vectors in s-byte floats and the coarse factor in FP64: the
-    operator with the factors rebuilt from the vertices (input gather and
-    entity records per local node, 24 vertex doubles per element, the gather
-    of the shared nodes), the patch solves (index, residual gather and
-    correction per patch node, an index per outside slot), the sum of the
-    corrections with the shared-node gather, the restriction, both coarse
-    sweeps, and the r and p/x vector updates."""
-    patch = E * (N + 3) ** 3
+    """Algorithmic HBM bytes of one two-scale PCG iteration as the path runs it, each array that a
+    kernel reads or writes counted once (gathers re-read through the caches), with the fine-level
+    vectors in s-byte floats and the coarse factor in FP64: the operator's element kernel, r updated
+    at the shared nodes with the gather of A p, r updated at the interiors with the restriction, the
+    coarse sweeps, the patch solves, and the sum of the corrections into x and p at the interiors and
+    at the shared nodes.  Neither A p at the shared nodes nor z is stored."""
+    interior = E * (N - 1) ** 3
+    shared, shared_global = n_local - interior, n_global - interior
     outside = E * ((N + 3) ** 3 - (N + 1) ** 3)
-    shared = n_local - E * (N - 1) ** 3
-    op = n_local * (s + 4) + 192 * E + 2 * s * n_global
-    fine = patch * (4 + 2 * s) + 4 * outside
-    assemble = s * patch + s * n_local + 2 * s * shared
-    coarse = s * n_local + 64 * E + 8 * coarse_entries
-    vectors = 3 * s * n_global + 5 * s * n_global
-    return op + fine + assemble + coarse + vectors
+    records = 432 * E
+    patch_index = 1208 * E if N >= PATCH_RECORDS_FROM else 4 * E * (N + 3) ** 3 + 4 * outside
+    element = operator_bytes(E, N, n_local, n_global, s)[0]
+    r_shared = s * shared + 2 * s * shared_global
+    r_interior = records + s * n_global + 2 * s * interior + 8 * 12 * E  # eight parts and their places
+    patches = patch_index + s * n_global + s * n_local + s * outside
+    px_interior = records + s * n_local + s * outside + 4 * s * interior + s * shared
+    px_shared = s * shared + 4 * s * shared_global
+    return element + r_shared + r_interior + 8 * coarse_entries + patches + px_interior + px_shared
 
 
 def pcg_roofline(E, N, n_local, n_global, coarse_entries, info, time_s, refined):
@@ -114,8 +129,9 @@ def pcg_roofline(E, N, n_local, n_global, coarse_entries, info, time_s, refined)
     bytes at the 8 TB/s peak over the measured solve time."""
     if refined:
         inner = info["iterations"] * pcg_iteration_bytes(E, N, n_local, n_global, coarse_entries, 4)
-        # each outer step: FP64 operator, true residual, scaling to FP32, FP64 update of x
-        outer = (info["outer"] + 1) * (n_local * 12 + 192 * E + 16 * n_global + 56 * n_global)
+        # each outer step: FP64 operator, true residual (b, A x, mask, r), r scaled to FP32 with its norm and
+        # the correction cleared, FP64 update of x
+        outer = (info["outer"] + 1) * (sum(operator_bytes(E, N, n_local, n_global, 8)) + (25 + 20 + 20) * n_global)
         total = inner + outer
     else:
         total = info["iterations"] * pcg_iteration_bytes(E, N, n_local, n_global, coarse_entries, 8)
