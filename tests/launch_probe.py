@@ -1,5 +1,5 @@
-"""Launch shapes as the library chooses them, read on the host: the coarse sweeps'
-launches of a mesh and the packing of the element kernels.  A few lines are
+"""What the library's set-up decides, read on the host: the coarse sweeps' launches
+of a mesh, the packing of the element kernels, whether a mesh has patch records.  A few lines are
 compiled with the library's host header and the packing functions of its kernel
 header, and linked to it."""
 import ctypes
@@ -33,6 +33,20 @@ extern "C" int launches(const double* vtx, int64_t nv, const int64_t* hex, int64
     }
   return n;
 }
+extern "C" int has_patch_records(const double* vtx, int64_t nv, const int64_t* hex, int64_t nh, int order) {
+  HostTables T;
+  build_reference(T, order);
+  build_numbering(T, hex, nh, nv);
+  build_geometry(T, vtx, hex);
+  build_patches(T, hex);
+  std::vector<int32_t> pidx, pdst;
+  try {
+    build_patch_records(T, pidx, pdst);
+  } catch (const Error&) {
+    return 0;
+  }
+  return pidx.size() == (size_t)nh * 250 && pdst.size() == (size_t)nh * 52;
+}
 @PACKING@
 template <int N>
 static int one(int what) { return what == 0 ? line_epb<N>() : fdm_ppb<N>(); }
@@ -63,13 +77,22 @@ def build(folder):
     return ctypes.CDLL(lib)
 
 
+def _arguments(mesh):
+    vtx, hexes = np.ascontiguousarray(mesh.vtx, dtype=np.float64), np.ascontiguousarray(mesh.hex, dtype=np.int64)
+    return (vtx, hexes), (vtx.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(len(vtx)),
+                          hexes.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(len(hexes)))
+
+
+def has_patch_records(lib, mesh, order):
+    kept, args = _arguments(mesh)
+    return bool(lib.has_patch_records(*args, order))
+
+
 def coarse_launches(lib, mesh):
     """[(forward, rows per wave, rows beyond 128 entries, workgroups)] of one coarse solve."""
-    vtx, hexes = np.ascontiguousarray(mesh.vtx, dtype=np.float64), np.ascontiguousarray(mesh.hex, dtype=np.int64)
+    kept, args = _arguments(mesh)
     out = np.zeros(1024, dtype=np.int32)
-    n = lib.launches(vtx.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(len(vtx)),
-                     hexes.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(len(hexes)),
-                     out.ctypes.data_as(ctypes.c_void_p), out.size)
+    n = lib.launches(*args, out.ctypes.data_as(ctypes.c_void_p), out.size)
     assert n >= 0
     return [tuple(int(v) for v in row) for row in out[:4 * n].reshape(-1, 4)]
 
