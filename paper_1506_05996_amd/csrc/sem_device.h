@@ -146,9 +146,6 @@ struct sem_mesh_s {
 
 namespace sem {
 
-constexpr int kThreads = 256;
-inline int64_t blocks_of(int64_t n, int t = kThreads) { return n < 1 ? 1 : (n + t - 1) / t; }
-
 // internal operations on a handle (all stream-ordered, no synchronisation)
 template <typename T>
 void apply_A(sem_mesh m, const T* u, T* y, hipStream_t s);

@@ -175,9 +175,9 @@ OpCoef<T> op_coef(sem_mesh m) {
   return oc;
 }
 
-// element kernel launches; with dpart, each workgroup also leaves its share
-// of u . y over the element interiors in dpart[block] (the grid size is
-// returned so the caller knows how many)
+// element kernel launches; with dpart, each workgroup also leaves its share of
+// u^T A u in dpart[block], over all local nodes, so that the shares' sum is the whole
+// scalar product (the grid size is returned so the caller knows how many)
 template <int N, typename T, int EPB, bool GEO = false, bool KN = false>
 int64_t launch_ax_tile(sem_mesh m, const T* u, T* y, double* dpart, hipStream_t s) {
   if constexpr (tile_ok<N>(EPB)) {
@@ -624,9 +624,14 @@ void ensure_side_stream(sem_mesh m) {
 // The exact solve's few launches run before them on the caller's stream: the
 // patch solves fill every CU, so that each height waited for their workgroups
 // to end, and the hand-overs between the streams cost about 10 us each (beside /
-// before: 24^3, N = 7 PCG 18.0 / 17.5 ms, 56^3 212.8 / 208.8 ms, 40^3 refined 59.0 /
-// 59.7 ms; preconditioner alone 16^3 79 / 72 us, 40^3 826 / 809 us).  A K-cycle of
-// some 200 small launches is worth hiding.
+// before, N = 7: preconditioner alone 24^3 177 / 170 us FP64 and 133 / 127 FP32, 40^3
+// 797 / 779 and 623 / 605, 56^3 2221 / 2180 and 1718 / 1667; PCG 24^3 17.5 / 17.2 ms,
+// 40^3 refined 60.8 / 59.3, 56^3 216 / 213 and refined 163 / 160).  At N = 9 the patch
+// solves leave room and beside is the faster (30^3 559 / 585 us and 427 / 459, PCG
+// 77.5 / 79.0 ms and 55.6 / 57.3); the one order is kept all the same.  Against the graph of
+// one launch per height that ran beside them earlier the preconditioner alone at 56^3
+// takes 2180 / 2187 us FP64 and 1667 / 1651 FP32, the latter 1% slower.  A K-cycle of some
+// 200 small launches is worth hiding.
 bool coarse_beside(sem_mesh m) { return !m->one_stream && m->coarse_solver == SEM_COARSE_AMG; }
 
 // what follows on s runs beside the coarse chain on the returned stream

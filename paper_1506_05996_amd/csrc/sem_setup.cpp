@@ -953,8 +953,11 @@ void build_patches(HostTables& T, const int64_t* hex) {
 // 0, 1, 2..N, N + 1, N + 2) with the global id base + ai a + aj b + ak c, and 26
 // entities of the outside slots (6 faces, 12 edges, 8 corners in ordinal order)
 // with the destination base + su u + sv v, (u, v) the position in the face or along
-// the edge.  [..][2] int32: base, strides (pack_coef) or kPatchNull.  Every entry of
-// ip and xdest is checked against its record.
+// the edge.  [..][2] int32: base, strides (pack_coef) or kPatchNull.  A class or an
+// entity comes whole from one entity of one element (build_patches decides NULL and
+// steps across faces by the signs of the three indices alone), whose ids and slots
+// are affine, so every mesh has records; every entry of ip and xdest is checked
+// against its record all the same.
 void build_patch_records(const HostTables& T, std::vector<int32_t>& pidx, std::vector<int32_t>& pdst) {
   const int N = T.N, n1 = T.n1, m = T.np, P1 = n1 * n1;
   const int64_t E = T.E, MMM = (int64_t)m * m * m, NX = T.nx;
