@@ -230,7 +230,7 @@ int64_t launch_ax(sem_mesh m, const T* u, T* y, double* dpart, hipStream_t s) {
     return launch_ax_line<N, T, true>(m, u, y, dpart, s);
   }
   if (epb == kTileLineStored) return launch_ax_line<N, T, false>(m, u, y, dpart, s);
-  switch (epb > 0 ? epb : ax_epb<N>()) {
+  switch (epb) {
     case 1: return launch_ax_tile<N, T, 1>(m, u, y, dpart, s);
     case 2: return launch_ax_tile<N, T, 2>(m, u, y, dpart, s);
     case 4: return launch_ax_tile<N, T, 4>(m, u, y, dpart, s);
@@ -239,11 +239,17 @@ int64_t launch_ax(sem_mesh m, const T* u, T* y, double* dpart, hipStream_t s) {
   }
 }
 
+// the largest compiled packing (kTileCandidates) of at most ax_epb elements
+template <int N>
+constexpr int packed_tile() {
+  return ax_epb<N>() >= 4 ? 4 : ax_epb<N>() >= 2 ? 2 : 1;
+}
+
 int default_tile(int N) {
   switch (N) {
 #define CASE(NN) \
   case NN:       \
-    return ax_epb<NN>();
+    return packed_tile<NN>();
     CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14)
     CASE(15)
 #undef CASE
@@ -1083,14 +1089,14 @@ double read_scalar(sem_mesh m, int idx, hipStream_t s) {
 // tolerance returns at once; after a breakdown x keeps the last finite iterate
 // (the vector updates skip themselves once the flag is set).
 //
-// One iteration is nine launches and the coarse solve's (two sums fewer on
-// small meshes): the operator's element kernel with p . A p; alpha; r -= alpha A p
-// at the shared nodes, with the gather of A p, then at the interiors, with r . r
-// and the coarse restriction; r . r to the host; the coarse solve; the patch
-// solves with r . z; beta; the sum of the corrections into x and p at the
-// interiors, then at the shared nodes.  The
-// scalar products need no assembled vector, so neither A p at the shared nodes
-// nor z is ever stored.  Against the gathers and vector updates as passes of
+// One iteration is nine launches and the coarse solve's (two sums fewer up to
+// kConsumerSum partial sums, a chunk sum more for each beyond kOneSum): the
+// operator's element kernel with p . A p; alpha; r -= alpha A p at the shared nodes,
+// with the gather of A p, then at the interiors, with r . r and the coarse
+// restriction; r . r to the host; the coarse solve; the patch solves with r . z;
+// beta; the sum of the corrections into x and p at the interiors, then at the
+// shared nodes.  The scalar products need no assembled vector, so neither A p at the
+// shared nodes nor z is ever stored.  Against the gathers and vector updates as passes of
 // their own: PCG to 1e-10 at 24^3, N = 7 19.2 -> 17.4 ms, 4^3,
 // N = 4 3.0 -> 1.8 ms, 40^3 refined 62.8 -> 58.7 ms.
 template <typename T>
