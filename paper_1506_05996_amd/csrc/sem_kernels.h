@@ -1143,7 +1143,7 @@ constexpr int fdm_threads() {
 // row S[ho][even j]; rows are read with wave-uniform addresses (scalar loads
 // feeding the FMAs) in a rolled loop, so S is not hoisted into registers.
 //   pencil_St: out = S^T x     (x in LDS, stride apart)
-//   pencil_S:  y = scale S v    (y in LDS)
+//   pencil_S:  y = S v          (y in LDS)
 template <int m, typename T>
 __device__ __forceinline__ void pencil_St(const T* __restrict__ Sp, const T* x, int stride, T (&out)[m]) {
   constexpr int ho = m / 2, he = m - ho;
@@ -1168,7 +1168,7 @@ __device__ __forceinline__ void pencil_St(const T* __restrict__ Sp, const T* x, 
 }
 
 template <int m, typename T>
-__device__ __forceinline__ void pencil_S(const T* __restrict__ Sp, const T (&v)[m], T* y, int stride, T scale) {
+__device__ __forceinline__ void pencil_S(const T* __restrict__ Sp, const T (&v)[m], T* y, int stride) {
   constexpr int ho = m / 2, he = m - ho;
 #pragma unroll 1
   for (int a = 0; a < ho; ++a) {
@@ -1178,15 +1178,15 @@ __device__ __forceinline__ void pencil_S(const T* __restrict__ Sp, const T (&v)[
     for (int j = 0; j < he; ++j) ev += sr[j] * v[j];
 #pragma unroll
     for (int j = 0; j < ho; ++j) od += sr[he + j] * v[he + j];
-    y[a * stride] = (ev + od) * scale;
-    y[(m - 1 - a) * stride] = (ev - od) * scale;
+    y[a * stride] = ev + od;
+    y[(m - 1 - a) * stride] = ev - od;
   }
   if constexpr (m % 2 == 1) {
     const T* sr = Sp + ho * m;
     T ev = T(0);
 #pragma unroll
     for (int j = 0; j < he; ++j) ev += sr[j] * v[j];
-    y[ho * stride] = ev * scale;
+    y[ho * stride] = ev;
   }
 }
 
@@ -1301,18 +1301,23 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
     for (int b = 0; b < m; ++b) col[b * m] = o[b];
   }
   __syncthreads();
-  // pass 3: zeta, S^T, diagonal, S  (lane owns pencil (a = p0, b = p1)); with
-  // epart, the workgroup's share of r . z: with y = S^T r the transformed
-  // residual, r_s . z_s = 8/(hx hy hz) sum y^2 / diagonal, all in registers here
+  // pass 3: zeta, S^T, diagonal, S  (lane owns pencil (a = p0, b = p1)).  The volume
+  // factor 8/(hx hy hz) is divided into kappa and c here, so that with epart, the
+  // workgroup's share of r . z, y = S^T r the transformed residual gives
+  // r_s . z_s = sum y^2 / diagonal from what is in registers, each product as large
+  // as a node's share of r . z (y^2 over the diagonal without the factor left the
+  // FP64 range where r . z does not).
   double en = 0.0;
   if (act) {
-    const T hx = hg[e * 3 + 0], hy = hg[e * 3 + 1], hz = hg[e * 3 + 2];
-    const T ihx2 = T(4) / (hx * hx), ihy2 = T(4) / (hy * hy), ihz2 = T(4) / (hz * hz);
+    const T hx = hg[e * 3 + 0], hy = hg[e * 3 + 1], hz = hg[e * 3 + 2], vol = hx * hy * hz;
+    const T ihx2 = T(0.5) / (hx * hx), ihy2 = T(0.5) / (hy * hy), ihz2 = T(0.5) / (hz * hz);  // 4 / h^2 over 8
     T kp = kap, c0 = cm;
     if (ke != nullptr) {  // the subdomain's own element's coefficients
       kp = ke[e];
       c0 = ce[e];
     }
+    kp *= vol;
+    c0 *= T(0.125) * vol;
     T* pen = Xp + p1 * m + p0;
     const T dab = sL[p0] * ihx2 + sL[p1] * ihy2;
     pencil_St<m, T>(S, pen, MM, o);
@@ -1322,12 +1327,7 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
       o[c] = yc * recip_pos(kp * (dab + sL[c] * ihz2) + c0);
       if (epart != nullptr) en += (double)yc * (double)o[c];
     }
-    if (epart != nullptr) {  // the sizes read again (cached): held through the pass they would spill
-      int64_t eh = e;
-      asm volatile("" : "+v"(eh));
-      en *= 8.0 / ((double)hg[eh * 3] * (double)hg[eh * 3 + 1] * (double)hg[eh * 3 + 2]);
-    }
-    pencil_S<m, T>(S, o, pen, MM, T(1));
+    pencil_S<m, T>(S, o, pen, MM);
   }
   if (epart != nullptr) {
     for (int q = 32; q > 0; q >>= 1) en += __shfl_xor(en, q);
@@ -1345,16 +1345,15 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
     T* col = Xp + p1 * MM + p0;
 #pragma unroll
     for (int b = 0; b < m; ++b) v[b] = col[b * m];
-    pencil_S<m, T>(S, v, col, m, T(1));
+    pencil_S<m, T>(S, v, col, m);
   }
   __syncthreads();
-  // pass 5: xi, S, and the volume factor 8/(hx hy hz)
+  // pass 5: xi, S
   if (act) {
     T* row = Xp + p1 * MM + p0 * m;
-    const T vscale = T(8) / (hg[e * 3 + 0] * hg[e * 3 + 1] * hg[e * 3 + 2]);
 #pragma unroll
     for (int a = 0; a < m; ++a) v[a] = row[a];
-    pencil_S<m, T>(S, v, row, 1, vscale);
+    pencil_S<m, T>(S, v, row, 1);
   }
   __syncthreads();
   // Results out, driven by the destination: the element's own nodes to zc in

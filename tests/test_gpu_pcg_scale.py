@@ -32,3 +32,28 @@ def test_pcg_kappa_scale(k, N, kappa, pc):
         assert abs(info["iterations"] - one["iterations"]) <= 2 + one["iterations"] // 50
         assert float(torch.linalg.norm(x * kappa - ref)) <= 1e-6 * float(torch.linalg.norm(ref))
     M.close()
+
+
+@pytest.mark.parametrize("pc", [1, 3])
+@pytest.mark.parametrize("length,scale", [(1e-20, 1e-140), (1e20, 1e140), (1e-12, 1e-140)])
+@pytest.mark.parametrize("k,N", [((4, 3, 3), 3), ((3, 3, 2), 7)])
+def test_pcg_box_and_load_scale(k, N, length, scale, pc):
+    """Very small and very large boxes under very small and very large loads: A grows with the
+    length, so the solution is the unit box's times scale / length.  Same bounds as above."""
+    from paper_1506_05996_amd import sem
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[pcg scale] k={k} N={N} length={length} scale={scale} pc={pc}", flush=True)
+    b, ref, one = None, None, None
+    for lx, f in ((1.0, 1.0), (length, scale)):
+        m = meshgen.cube_mesh(k, lengths=(lx, lx, lx), perturb=0.1, seed=N)
+        M = sem.Mesh(m.vtx, m.hex, N, autotune=False)
+        if b is None:
+            b = np.random.default_rng(N).uniform(-1.0, 1.0, M.n_global) * (M.boundary_mask() == 0)
+        x, info = M.solve(torch.tensor(b * f, device="cuda:0"), pc=pc, rtol=1e-10)
+        M.close()
+        if ref is None:
+            ref, one = x, info
+            continue
+        assert abs(info["iterations"] - one["iterations"]) <= 2
+        assert float(torch.linalg.norm(x * (length / scale) - ref)) <= 1e-6 * float(torch.linalg.norm(ref))
