@@ -1306,7 +1306,8 @@ fdm_kernel(const T* __restrict__ r, T* __restrict__ zc, T* __restrict__ zx, cons
   // workgroup's share of r . z, y = S^T r the transformed residual gives
   // r_s . z_s = sum y^2 / diagonal from what is in registers, each product as large
   // as a node's share of r . z (y^2 over the diagonal without the factor left the
-  // FP64 range where r . z does not).
+  // FP64 range where r . z does not).  Fine preconditioner at 40^3, N = 7, factor applied
+  // to z at the end / so: 572 / 563 us FP64, 371 / 353 us FP32.
   double en = 0.0;
   if (act) {
     const T hx = hg[e * 3 + 0], hy = hg[e * 3 + 1], hz = hg[e * 3 + 2], vol = hx * hy * hz;
